@@ -793,6 +793,121 @@ __host__ __device__ inline void engine_column_l(DevState &s, const double *raw, 
   }
 }
 
+// engine_column for L <= 3 in two parts, for a kernel whose iteration waits for the
+// column: engine_gather<L> reads every entry of the state the column may use (ring
+// indices wrapped, entries with negative index zero) and forms lambda, all before the
+// products are known; engine_step<L> computes from registers, with the expressions of
+// engine_column (a term with a zero factor changes no bit of what it is subtracted
+// from), and also returns the coefficients of the sweep with t = c - 1.
+template <int L>
+struct EngineIn {
+  double sym[L];                                // g_{c-2L+q, c} by symmetry
+  double row[L > 1 ? L - 1 : 1][2 * L - 1];     // row[m-1][q] = g_{c-2L+q, c-L+m}, q < L + m
+  double diag[L > 1 ? L - 1 : 1];               // g_{c-L+m, c-L+m}
+  double gtt, gpt;                              // g_{t,t}, g_{t-1,t}
+  double dlt1, lam, zeta1, gaml, dltl, sigma;   // entries t-1 and t-L; sigma_t
+  double beta, abs_tol;
+};
+
+struct SweepCoef {
+  double gam, dm1, inv_del, inv_eta, zm1;
+};
+
+template <int L>
+__host__ __device__ inline EngineIn<L> engine_gather(const DevState &s, int c) {
+  const int t = c - 1;
+  auto g = [&](int r, int q) {
+    const double v = s.g[q & (kGRing - 1)][r - q + 2 * kLMax];
+    return r >= 0 && q >= 0 ? v : 0.0;
+  };
+  EngineIn<L> in;
+#pragma unroll
+  for (int q = 0; q < L; ++q) {
+    const int r = c - 2 * L + q;
+    in.sym[q] = r >= 0 ? g(c - L, r + L) : 0.0;
+  }
+#pragma unroll
+  for (int m = 1; m < L; ++m) {
+    const int j = c - L + m;
+#pragma unroll
+    for (int q = 0; q < L + m; ++q) in.row[m - 1][q] = g(c - 2 * L + q, j);
+    in.diag[m - 1] = g(j, j);
+  }
+  in.gtt = g(t, t);
+  in.gpt = g(t - 1, t);
+  const int t1 = (t >= 1 ? t - 1 : 0) & (kTRing - 1);
+  const int tl = (t >= L ? t - L : 0) & (kTRing - 1);
+  in.dlt1 = s.dlt[t1];
+  in.zeta1 = s.zeta[t1];
+  in.lam = in.dlt1 / s.eta[t1];
+  in.gaml = s.gam[tl];
+  in.dltl = s.dlt[tl];
+  in.sigma = s.sigma[t >= 0 && t < kLMax ? t : 0];
+  in.beta = s.beta;
+  in.abs_tol = s.abs_tol;
+  return in;
+}
+
+template <int L>
+__host__ __device__ inline SweepCoef engine_step(DevState &s, const EngineIn<L> &in,
+                                                 const double *raw, int c, double *hist) {
+  constexpr int W = 2 * L + 1;
+  const int t = c - 1;
+  double gc[W];
+#pragma unroll
+  for (int q = 0; q < L; ++q) gc[q] = in.sym[q];
+  gc[L] = c - L >= 0 ? raw[0] : 0.0;
+#pragma unroll
+  for (int m = 1; m <= L; ++m) gc[L + m] = c - L + m >= 0 ? raw[m] : 0.0;
+#pragma unroll
+  for (int m = 1; m < L; ++m) {
+    double v = gc[L + m];
+#pragma unroll
+    for (int q = 0; q < L + m; ++q) v -= in.row[m - 1][q] * gc[q];
+    gc[L + m] = c - L + m >= 0 ? v / in.diag[m - 1] : 0.0;
+  }
+  double arg = gc[2 * L];
+#pragma unroll
+  for (int q = 0; q < 2 * L; ++q) arg -= gc[q] * gc[q];
+  bool broken = !(isfinite(arg) && arg > 0.0);
+  const double gcc = sqrt(arg);
+  const double corr = t >= 1 ? in.gpt * in.dlt1 : 0.0;
+  const double gtc = gc[2 * L - 1];
+  const double gam = (t < L ? gtc + in.sigma * in.gtt - corr
+                            : in.gtt * in.gaml + gtc * in.dltl - corr) / in.gtt;
+  const double dlt = (t < L ? gcc : gcc * in.dltl) / in.gtt;
+  broken = broken || !(isfinite(gam) && isfinite(dlt) && dlt > 0.0);
+  const double eta = t == 0 ? gam : gam - in.lam * in.dlt1;
+  const double zeta = t == 0 ? in.beta : -in.lam * in.zeta1;
+  broken = broken || !(isfinite(eta) && eta > 0.0 && isfinite(zeta));
+  const bool sq = isfinite(arg) && arg > 0.0;
+  if (sq) gc[2 * L] = gcc;
+#pragma unroll
+  for (int q = 0; q < W; ++q) gref(s, c - 2 * L + q, c) = gc[q];
+  s.cols = c;
+  SweepCoef cf{gam, t >= 1 ? in.dlt1 : 0.0, 1.0 / dlt, 1.0 / eta, t >= 1 ? in.zeta1 : 0.0};
+  if (broken) {
+    s.status = kBroken;
+    s.last_t = t - 1;
+    return cf;
+  }
+  s.gam[t & (kTRing - 1)] = gam;
+  s.dlt[t & (kTRing - 1)] = dlt;
+  s.eta[t & (kTRing - 1)] = eta;
+  s.zeta[t & (kTRing - 1)] = zeta;
+  if (hist != nullptr && t < s.hist_cap) {
+    hist[4 * t + 0] = gam;
+    hist[4 * t + 1] = dlt;
+    hist[4 * t + 2] = eta;
+    hist[4 * t + 3] = zeta;
+  }
+  if (t >= 1 && fabs(zeta) < in.abs_tol) {
+    s.status = kConverged;
+    s.last_t = t;
+  }
+  return cf;
+}
+
 // ---------------------------------------------------------------------------
 // Coefficients of one sweep
 // ---------------------------------------------------------------------------

@@ -10,7 +10,7 @@
 // return at once.  A breakdown (Sec. 2.2, "Square root breakdowns") restarts
 // Alg. 1 from the most recent iterate with a recomputed residual, keeping the
 // original reference norm of the stopping test.
-#include "plcg_internal.h"
+#include "plcg_team_launch.h"
 
 #include "../../include/plcg.h"
 
@@ -51,7 +51,15 @@ constexpr long long kLargeVector = 96LL << 20;   // vectors worth storing non-te
 // Iterations one resident launch may run (about a second for the largest
 // resident systems); longer runs use the streaming kernels.
 constexpr int kResIterCap = 1 << 20;
+// Iterations one team launch may run (a few seconds at most); its tags fit an int.
+constexpr int kTeamIterCap = 1 << 20;
+constexpr int kMaxDevices = 64;
 constexpr int kDefaultRestarts = 100;
+
+// A team launch needs all its workgroups on the GPU at once, so two of them at a time
+// would wait for each other: one runs on a device at a time (within the process;
+// across processes the kernel's bounded waits and the streaming sweeps take over).
+std::mutex g_team_mu[kMaxDevices];
 
 // Streaming cache hints for the sweeps of a solver whose vectors are `word`
 // bytes per unknown (measured on 2048^2 and 256^3 Poisson, the 2048^2 CSR
@@ -144,6 +152,10 @@ struct plcg_handle {
   int n = 0, nchunks = 0, blocks = 0;
   bool d3 = false;
   int res_kind = -1;              // operator kind of the resident kernels; -1: streaming
+  bool team = false;              // segments run as team launches
+  TeamGeom team_geom{};
+  void *team_mail = nullptr, *team_post = nullptr;
+  int team_base = 1;              // first tag of the next team launch
   int hint64 = 0, hint32 = 0;     // streaming cache hints of the FP64 / FP32-stored sweeps
   int sweep_nb[2] = {0, 0};       // streaming workgroups of the FP32 / FP64-stored sweeps (0: not chosen yet)
   bool pair64 = false, pair32 = false;   // the same sweeps update x on even t only
@@ -389,6 +401,53 @@ plcg_status residual(plcg_handle *h, const double *b, const double *x, double *r
   return PLCG_OK;
 }
 
+// One team launch of `tags` tags: the whole segment of Alg. 1 (or all of CG) from
+// z0 and x, state copy 1 in, copy 0 out, the last iterate into x once the launch
+// has ended well.  *ran false: not all workgroups got onto the GPU in time (other
+// work held it); nothing has changed then, and the handle streams from now on.
+plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratch, int imax,
+                     int tags, hipStream_t s, TimedLaunch &tl, bool *ran) {
+  *ran = false;
+  if (h->team_base > 0x7fffffff - tags) {
+    PLCG_HIP(hipMemsetAsync(h->team_mail, 0, team_mail_bytes(h->team_geom), s));
+    PLCG_HIP(hipMemsetAsync(h->team_post, 0, team_post_bytes(), s));
+    h->team_base = 1;
+  }
+  TeamArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.z0 = z0;
+  a.x = x;
+  a.x_out = scratch;
+  a.st_in = h->st[1];
+  a.st_out = h->st[0];
+  a.hs = h->hs_dev;
+  a.hist = h->hist;
+  a.mail = h->team_mail;
+  a.post = h->team_post;
+  a.g = h->team_geom;
+  a.base = h->team_base;
+  a.imax = imax;
+  h->team_base += tags;
+  plcg_status e;
+  std::lock_guard<std::mutex> lk(g_team_mu[h->device]);
+  if ((e = tl.begin_group()) != PLCG_OK) return e;
+  if (h->method == PLCG_METHOD_CG)
+    PLCG_HIP(launch_cg_team(a, h->d3, s));
+  else
+    PLCG_HIP(launch_plcg_team(a, h->l, h->d3, s));
+  tl.launched();
+  if ((e = tl.end_group()) != PLCG_OK) return e;
+  PLCG_HIP(wait_stream(h, s));
+  if (hstat(h)->lost == a.base) {
+    tl.set_units(tl.launches() - 1, 0);
+    h->team = false;
+    return PLCG_OK;
+  }
+  PLCG_HIP(launch_copy(scratch, x, h->n, s));
+  *ran = true;
+  return PLCG_OK;
+}
+
 struct Segment {
   int status, last_t, t_done, sweeps_run, final_slot;
   double rec;
@@ -407,9 +466,13 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
   int last_i = -1;
   const size_t first_launch = tl.launches();
   plcg_status e;
-  const bool resident = h->res_kind >= 0 && std::is_same<S, double>::value && m <= kResIterCap;
+  // whole: the segment runs in one launch (resident or team)
+  bool whole = h->res_kind >= 0 && std::is_same<S, double>::value && m <= kResIterCap;
   if constexpr (std::is_same<S, double>::value) {
-    if (resident) {
+    if (h->team && m <= kTeamIterCap) {
+      if ((e = run_team(h, ring[0], x, p[1], imax, imax + 2, s, tl, &whole)) != PLCG_OK) return e;
+      if (whole) last_i = 0;
+    } else if (whole) {
       // the whole segment in one resident launch: state copy 1 in, copy 0 out
       ResArgs ra;
       std::memset(&ra, 0, sizeof(ra));
@@ -433,7 +496,7 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
       last_i = 0;   // final state in copy 0
     }
   }
-  for (int i0 = 0; !resident && i0 <= imax; i0 += h->check_every, ++group) {
+  for (int i0 = 0; !whole && i0 <= imax; i0 += h->check_every, ++group) {
     const int i1 = std::min(imax + 1, i0 + h->check_every);
     if ((e = tl.begin_group()) != PLCG_OK) return e;
     for (int i = i0; i < i1; ++i) {
@@ -456,7 +519,7 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
   // after sweep last_t + l: enqueue the sweeps up to there that were not
   // enqueued yet.  They run as ordinary sweeps (t <= last_t) and carry the
   // state forward.
-  if (!resident && ds.status != kRunning) {
+  if (!whole && ds.status != kRunning) {
     const int need = std::min(imax, std::max(ds.last_t, -1) + l);
     if (need > last_i) {
       if ((e = tl.begin_group()) != PLCG_OK) return e;
@@ -478,14 +541,14 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
   // Iterations that ran: every sweep up to last_t + l (or the whole loop).
   out->t_done = ds.status == kRunning ? m : std::min(std::max(ds.last_t, 0), m);
   out->sweeps_run = std::min(imax, (ds.status == kRunning ? imax : ds.last_t + l)) + 1;
-  if (resident)
+  if (whole)
     tl.set_units(first_launch, (uint32_t)out->sweeps_run);
   else
     tl.keep(first_launch, (size_t)out->sweeps_run);
   out->rec = out->t_done == 0 ? ds.beta : std::fabs(ds.zeta[out->t_done % kTRing]);
   // The streaming sweeps left x at x_{t_done-1} if t_done is odd: add the last
   // step zeta_{t_done-1} p_{t_done-1} (p_{t_done-1} is intact in its buffer).
-  if (!resident && (sizeof(S) == 8 ? h->pair64 : h->pair32) && (out->t_done & 1)) {
+  if (!whole && (sizeof(S) == 8 ? h->pair64 : h->pair32) && (out->t_done & 1)) {
     const int tl1 = out->t_done - 1;
     PLCG_HIP(launch_x_step<S>(x, p[tl1 & 1], ds.zeta[tl1 % kTRing], h->n, s));
   }
@@ -700,8 +763,11 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
   int group = 0;
   bool stopped = false;
   const size_t first_launch = tl.launches();
-  const bool resident = h->res_kind >= 0 && maxit <= kResIterCap;
-  if (resident) {
+  bool whole = h->res_kind >= 0 && maxit <= kResIterCap;   // all iterations in one launch
+  if (h->team && maxit <= kTeamIterCap) {
+    if ((e = run_team(h, h->cg_r, x, h->cg_q, maxit, 2 * maxit + 4, s, tl, &whole)) != PLCG_OK)
+      return e;
+  } else if (whole) {
     // all iterations in one resident launch: state copy 1 in, copy 0 out
     ResArgs ra;
     std::memset(&ra, 0, sizeof(ra));
@@ -722,7 +788,7 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
     tl.launched();
     if ((e = tl.end_group()) != PLCG_OK) return e;
   }
-  for (int k0 = 0; !resident && k0 < maxit; k0 += h->check_every, ++group) {
+  for (int k0 = 0; !whole && k0 < maxit; k0 += h->check_every, ++group) {
     const int k1 = std::min(maxit, k0 + h->check_every);
     if ((e = tl.begin_group()) != PLCG_OK) return e;
     for (int k = k0; k < k1; ++k) {
@@ -740,7 +806,7 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
       break;
     }
   }
-  if (resident) {
+  if (whole) {
     *final_slot = 0;
   } else if (!stopped) {
     // Form rho_maxit and the stopping test of the last iterate (no streaming).
@@ -757,9 +823,9 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
   // Paired updates left x at x_{iters-1} if iters is odd: add alpha_{iters-1}
   // p_{iters-1} (p_{iters-1} is intact in its buffer, alpha_{iters-1} the last
   // alpha formed).
-  if (!resident && h->pair64 && (iters & 1))
+  if (!whole && h->pair64 && (iters & 1))
     PLCG_HIP(launch_x_step<double>(x, h->cg_p[(iters - 1) & 1], ds.cg_alpha, h->n, s));
-  if (resident)
+  if (whole)
     tl.set_units(first_launch, (uint32_t)(2 * iters));   // stands for sweeps A and B
   else
     tl.keep(first_launch, 2 * (size_t)iters);   // sweeps A and B of iterations 0 .. iters-1
@@ -1178,6 +1244,16 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
     else if (cfg->launch_mode == PLCG_LAUNCH_RESIDENT)
       return fail(PLCG_E_INVALID, "PLCG_LAUNCH_RESIDENT: too many stored entries");
   }
+  // Team launches: FP64 solves of the constant stencils that AUTO would stream.  A caller
+  // who names the launch mode or the x cadence gets the sweeps that have them.
+  const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
+  int cus = 0;
+  if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO && h->res_kind < 0 &&
+      h->precision == PLCG_PREC_FP64 && stencil && !h->var && h->device >= 0 &&
+      h->device < kMaxDevices &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess)
+    h->team = team_plan(pl ? 1 : 0, h->l, h->d3, h->op.nx, h->op.ny, h->op.nz, cus,
+                        &h->team_geom);
   return PLCG_OK;
 }
 
@@ -1255,6 +1331,14 @@ plcg_status plcg_create(const plcg_operator_desc *op, const plcg_config *cfg, pl
   if (e == PLCG_OK && op->kind == PLCG_OP_CSR) e = copy_csr(h, op);
   if (e == PLCG_OK && h->var) e = copy_var(h, op);
   if (e == PLCG_OK) e = finish_setup(h, op, cfg, res_ok);
+  if (e == PLCG_OK && h->team) {
+    const size_t mail = team_mail_bytes(h->team_geom);
+    e = dev_alloc(h, &h->team_mail, mail);
+    if (e == PLCG_OK) e = dev_alloc(h, &h->team_post, team_post_bytes());
+    if (e == PLCG_OK && (hipMemset(h->team_mail, 0, mail) != hipSuccess ||
+                         hipMemset(h->team_post, 0, team_post_bytes()) != hipSuccess))
+      e = fail(PLCG_E_HIP, "clearing the team mail failed");
+  }
   if (e != PLCG_OK) {
     release(h);
     delete h;
@@ -1439,8 +1523,8 @@ plcg_status plcg::check_workspace_solve(const plcg_operator_desc *op, const plcg
 }
 
 plcg_status plcg::solve_in_workspace(const plcg_operator_desc *op, const plcg_config *cfg,
-                                     void *ws, size_t ws_bytes, const double *d_b, double *d_x,
-                                     double tol, int32_t maxit, void *stream, plcg_result *out) {
+                                     void *ws, size_t ws_bytes, void *team_ws,
+                                     const double *d_b, double *d_x, double tol, int32_t maxit, void *stream, plcg_result *out) {
   plcg_handle h;
   bool res_ok = false;
   Workspace w;
@@ -1458,6 +1542,12 @@ plcg_status plcg::solve_in_workspace(const plcg_operator_desc *op, const plcg_co
   PLCG_HIP(hipMemcpyAsync(h.st[1], &init, sizeof(init), hipMemcpyHostToDevice, s));
   PLCG_HIP(hipMemsetAsync(h.part[0], 0, 2 * kPartBytes, s));
   PLCG_HIP(hipMemsetAsync(h.hs_dev, 0, sizeof(HostStatus), s));
+  if (h.team) {
+    // mail left by earlier calls carries tags of its own: clear what this call reads
+    h.team_post = team_ws;
+    h.team_mail = static_cast<char *>(team_ws) + team_post_bytes();
+    PLCG_HIP(hipMemsetAsync(team_ws, 0, team_post_bytes() + team_mail_bytes(h.team_geom), s));
+  }
   PLCG_HIP(hipStreamSynchronize(s));
   return do_solve(&h, d_b, d_x, tol, maxit, stream, out);
 }

@@ -66,6 +66,8 @@ struct HostStatus {
   double beta;        // ||r_0|| of the current segment
   double rref;        // reference norm of the stopping test (caller's ||b - A x0||)
   double sumsq;       // result of the last plain reduction (residual norms)
+  int32_t lost;       // base tag of the last team launch that gave up waiting (0: none)
+  int32_t pad;
 };
 
 // Scalar state of one solve segment.  Two copies alternate between launches:
@@ -316,14 +318,5 @@ int64_t batch_op_unknowns(const plcg_batch *b, int32_t op_id);
 int32_t edge_weights(int nx, int ny, int nz, bool d3, const double *cx, const double *cy,
                      const double *cz, bool jacobi, double *wx, double *wy, double *wz,
                      double *dd);
-
-// A whole solve (as plcg_create + plcg_solve) in ws_bytes of device memory at
-// ws, with no device or pinned host allocation; 2D and 3D stencil operators.
-// check_workspace_solve makes the same argument checks without any HIP call.
-int32_t check_workspace_solve(const plcg_operator_desc *op, const plcg_config *cfg,
-                              size_t ws_bytes);
-int32_t solve_in_workspace(const plcg_operator_desc *op, const plcg_config *cfg, void *ws,
-                           size_t ws_bytes, const double *d_b, double *d_x, double tol,
-                           int32_t maxit, void *stream, plcg_result *out);
 
 }  // namespace plcg

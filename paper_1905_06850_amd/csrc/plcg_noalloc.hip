@@ -13,7 +13,7 @@
 // what must start at zero.  Calls on one device are serialised here (a second
 // thread waits until the first call has returned), so they never overlap
 // within the process.
-#include "plcg_internal.h"
+#include "plcg_team_launch.h"
 
 #include <mutex>
 #include <string>
@@ -24,9 +24,12 @@ constexpr size_t kScratchBytes = (size_t)PLCG_NOALLOC_BYTES;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// The mail of team launches, beside the PLCG_NOALLOC_BYTES the work vectors share.
+static __device__ __align__(256) unsigned char team_scratch[plcg::kTeamWsBytes];
 
 std::mutex g_mu[kMaxDevices];
 void *g_scratch[kMaxDevices] = {};
+void *g_team_scratch[kMaxDevices] = {};
 
 }  // namespace
 
@@ -47,16 +50,18 @@ plcg_status plcg_solve_noalloc(const plcg_operator_desc *op, const plcg_config *
     return plcg::set_last_error(PLCG_E_INVALID, "device index beyond the supported 64");
   std::lock_guard<std::mutex> lk(g_mu[dev]);
   if (g_scratch[dev] == nullptr) {
-    void *ptr = nullptr;
+    void *ptr = nullptr, *team = nullptr;
     he = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    if (he != hipSuccess || ptr == nullptr)
+    if (he == hipSuccess) he = hipGetSymbolAddress(&team, HIP_SYMBOL(team_scratch));
+    if (he != hipSuccess || ptr == nullptr || team == nullptr)
       return plcg::set_last_error(
           PLCG_E_HIP, (std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(he))
                           .c_str());
     g_scratch[dev] = ptr;
+    g_team_scratch[dev] = team;
   }
-  return plcg::solve_in_workspace(op, cfg, g_scratch[dev], kScratchBytes, d_b, d_x, tol, maxit,
-                                  stream, out);
+  return plcg::solve_in_workspace(op, cfg, g_scratch[dev], kScratchBytes, g_team_scratch[dev], d_b,
+                                  d_x, tol, maxit, stream, out);
 }
 
 }  // extern "C"

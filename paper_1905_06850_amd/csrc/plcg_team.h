@@ -1,0 +1,187 @@
+// Geometry and arguments of the team kernels (plcg_team.hip): how a grid is cut
+// into tiles, one per workgroup, and where a tile's mail lies.  Plain C++ apart
+// from the pointers, so that the host and the tests can check it.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#if defined(__HIP__)
+#define PLCG_HD __host__ __device__
+#else
+#define PLCG_HD
+#endif
+
+namespace plcg {
+
+constexpr int kTeamWaves = 15;        // streaming waves per workgroup, beside one owner wave
+constexpr int kTeamTiles = 256;       // tiles at most (one workgroup per CU)
+constexpr int kTeamRing = 16;         // slots of the posted products, by column
+constexpr int kTeamProducts = 8;      // words of a workgroup's products of a column: a line
+                                      // of 128 bytes of its own, l + 1 <= 4 of them used
+constexpr int kTeamLMax = 3;          // deepest pipeline with a team kernel
+constexpr size_t kTeamMailMax = (size_t)32 << 20;
+constexpr int kWordBytes = 16;        // a posted double: {low, tag, high, tag}
+
+// Words of a wave's row of an x face: its v words, in cache lines of their own.
+PLCG_HD constexpr int team_xpitch(int v) { return (v + 7) / 8 * 8; }
+
+// A grid of nx * ny * nz unknowns (x fastest) in the axes of the team kernels:
+// x runs over the lanes of a wave, y over waves, z over waves and then over the V
+// unknowns of a thread.  A 2D grid enters as (nx, 1, ny).  A tile is 64 x wy x
+// (wz * v) unknowns, and the workgroup that holds it has wy * wz streaming waves.
+struct TeamGeom {
+  int32_t nx, ny, nz;
+  int32_t gx, gy, gz;                 // tiles along each axis
+  int32_t wy, wz, v;
+  int32_t rx, ry, rz;                 // words of one x, y and z face of a tile
+  int32_t words;                      // words of a tile's mail: two faces of each kind
+};
+
+PLCG_HD inline int team_tiles(const TeamGeom &g) { return g.gx * g.gy * g.gz; }
+PLCG_HD inline int team_threads(const TeamGeom &g) { return 64 * (g.wy * g.wz + 1); }
+// Bytes of the face mail (two copies by parity) and of the posted products.
+inline size_t team_mail_bytes(const TeamGeom &g) {
+  return (size_t)2 * team_tiles(g) * g.words * kWordBytes;
+}
+constexpr size_t team_post_bytes() {
+  return (size_t)kTeamRing * kTeamTiles * kTeamProducts * kWordBytes;
+}
+
+// A streaming wave's place in the grid and its share of the mail, uniform in the wave:
+// byte offsets within one parity copy, to which a lane adds 16 times its number (z and
+// y faces; row v of a y face 64 v words on) or 16 times the row it stands for (x faces:
+// lanes 0 .. v-1 carry the west side of rows 0 .. v-1, lanes 32 .. 32+v-1 the east side).
+// Of the offsets only those are used whose neighbour tile exists and whose face the
+// wave touches (the flags).
+struct TeamPlace {
+  int wyi, wzi, sw;
+  bool west, east, zlo, zhi, ylo, yhi;   // a neighbour tile lies there and this wave touches it
+  int in_w, in_e, in_zlo, in_zhi, in_y;          // where this wave reads
+  int out_w, out_e, out_zlo, out_zhi, out_y;     // where it posts
+  int x0, y, z0;                                 // lane 0's unknown of row 0
+
+  PLCG_HD inline TeamPlace(const TeamGeom &g, int v, bool d3, int tile, int sw_) {
+    sw = sw_;
+    wyi = d3 ? sw % g.wy : 0;
+    wzi = d3 ? sw / g.wy : sw;
+    const int bx = tile % g.gx, byz = tile / g.gx;
+    const int by = d3 ? byz % g.gy : 0, bz = d3 ? byz / g.gy : byz;
+    const int gxy = g.gx * g.gy;
+    west = bx > 0;
+    east = bx < g.gx - 1;
+    zlo = wzi == 0 && bz > 0;
+    zhi = wzi == g.wz - 1 && bz < g.gz - 1;
+    ylo = d3 && wyi == 0 && by > 0;
+    yhi = d3 && wyi == g.wy - 1 && by < g.gy - 1;
+    // mail of a tile: x faces (west, east), y faces (low, high), z faces (low, high)
+    const int W = kWordBytes;
+    const int fe = g.rx, fyl = 2 * g.rx, fyh = fyl + g.ry, fzl = fyh + g.ry, fzh = fzl + g.rz;
+    const int row = (wyi * g.wz + wzi) * team_xpitch(v);
+    const int mine = tile * g.words;
+    in_w = (mine + row) * W;
+    in_e = (mine + fe + row) * W;
+    out_w = ((tile - 1) * g.words + fe + row) * W;
+    out_e = ((tile + 1) * g.words + row) * W;
+    in_zlo = (mine + fzl + wyi * 64) * W;
+    in_zhi = (mine + fzh + wyi * 64) * W;
+    out_zlo = ((tile - gxy) * g.words + fzh + wyi * 64) * W;
+    out_zhi = ((tile + gxy) * g.words + fzl + wyi * 64) * W;
+    in_y = (mine + (ylo ? fyl : fyh) + wzi * v * 64) * W;
+    out_y = ((ylo ? (tile - g.gx) * g.words + fyh : (tile + g.gx) * g.words + fyl) +
+             wzi * v * 64) * W;
+    x0 = bx * 64;
+    y = by * g.wy + wyi;
+    z0 = (bz * g.wz + wzi) * v;
+  }
+};
+
+// Unknowns per thread the team kernels are built for: those of kTeamWidths up to this, the
+// largest that fits 128 registers (four waves per SIMD) without spilling and a CU's 160 KB
+// of LDS.
+constexpr int team_vmax(int method_plcg, int l, bool d3) {
+  return !method_plcg ? (d3 ? 5 : 10)
+         : l == 1     ? (d3 ? 5 : 6)
+         : l == 2     ? (d3 ? 4 : 5)
+         : l == 3     ? 3
+                      : 0;
+}
+// Whether a p(l)-CG team kernel keeps x, and p, in LDS.
+constexpr bool team_x_in_lds(int l, int v, bool d3) {
+  return v >= (l == 1 ? 6 : l == 2 && !d3 ? 5 : 4);
+}
+constexpr bool team_p_in_lds(int l, int v, bool d3) {
+  return team_x_in_lds(l, v, d3) && !(d3 && l == 1);
+}
+constexpr int kTeamWidths[] = {2, 3, 4, 5, 6, 7, 8, 10};
+
+// Cuts the grid into at most `tiles` tiles with v unknowns per thread: of the
+// arrangements of up to kTeamWaves waves the one with the smallest faces, waves
+// then evened out over the tiles.  false: it does not fit.
+inline bool team_cut(int nx, int ny, int nz, int v, int tiles, TeamGeom *out) {
+  const int gx = (nx + 63) / 64;
+  long long best = -1;
+  for (int wy = 1; wy <= kTeamWaves && wy <= ny; ++wy) {
+    int wz = kTeamWaves / wy;
+    const int zrows = (nz + v - 1) / v;              // z extent in units of v
+    if (wz > zrows) wz = zrows;
+    const int gy = (ny + wy - 1) / wy, gz = (zrows + wz - 1) / wz;
+    if ((long long)gx * gy * gz > tiles) continue;
+    // the same tile counts with the waves spread evenly
+    const int ey = (ny + gy - 1) / gy, ez = (zrows + gz - 1) / gz;
+    // a wave keeps the halo of one y side only
+    if (gy > 1 && ey < 2) continue;
+    const long long faces = (gx > 1 ? 2LL * ey * ez * v : 0) + (gy > 1 ? 128LL * ez * v : 0) +
+                            (gz > 1 ? 128LL * ey : 0);
+    if (best >= 0 && faces >= best) continue;
+    best = faces;
+    TeamGeom g{};
+    g.nx = nx;
+    g.ny = ny;
+    g.nz = nz;
+    g.gx = gx;
+    g.gy = gy;
+    g.gz = gz;
+    g.wy = ey;
+    g.wz = ez;
+    g.v = v;
+    g.rx = gx > 1 ? ey * ez * team_xpitch(v) : 0;
+    g.ry = gy > 1 ? 64 * ez * v : 0;
+    g.rz = gz > 1 ? 64 * ey : 0;
+    g.words = 2 * (g.rx + g.ry + g.rz);
+    *out = g;
+  }
+  return best >= 0;
+}
+
+// The cut of a system the team kernels take.  More unknowns per thread mean fewer tiles,
+// whose sums arrive sooner, and longer sweeps.  Measured (us per iteration, v = 1 .. 5):
+//   p(2) 256^2 2.64 2.58 2.36 2.55 3.11, 512^2 - 3.23 2.84 2.74 3.17, 700 x 650 - 3.56
+//        3.60 2.97 3.17, 64^3 - 3.93 3.78 2.97: the owner's chain sets the pace, so v >= 3
+//        and few tiles, but x and p still in registers (v <= 4);
+//   p(1) 256^2 2.94 2.89 3.02 3.12 3.38, 512^2 - 3.28 3.30 3.50 3.62, 64^3 - 3.61 3.72
+//        3.40 3.46, p(3) 256^2 2.81 2.62 2.50, 512^2 - 3.26 2.77, 64^3 - 3.53 3.84:
+//        flat once the tiles number 128 or less;
+//   CG   256^2 4.47 4.35 4.65 4.86, 512^2 - 5.04 5.04 5.38: one product per sum, so tiles
+//        cost little.
+// So: the smallest v from `lo` up to `hi` with at most `cap` tiles, else hi, else the
+// smallest larger v that fits at all.  false: the system is too large (or too narrow: the
+// lanes of a wave lie along x), or its face mail would outgrow kTeamMailMax.
+inline bool team_plan(int method_plcg, int l, bool d3, int nx, int ny, int nz, int tiles,
+                      TeamGeom *out) {
+  if (tiles > kTeamTiles) tiles = kTeamTiles;
+  const int vmax = team_vmax(method_plcg, l, d3);
+  const int lo = method_plcg && l == 2 ? 3 : 2;
+  const int hi = !method_plcg ? 2 : l == 3 ? 3 : 4;
+  const int cap = !method_plcg ? kTeamTiles : l == 2 ? 64 : 128;
+  for (int pass = 0; pass < 2; ++pass)
+    for (int v : kTeamWidths) {
+      if (v > vmax) break;
+      if (pass == 0 ? (v < lo || v > hi) : v < hi) continue;
+      if (team_cut(nx, d3 ? ny : 1, d3 ? nz : ny, v, pass == 0 && cap < tiles ? cap : tiles, out))
+        return team_mail_bytes(*out) <= kTeamMailMax;
+    }
+  return false;
+}
+
+}  // namespace plcg
