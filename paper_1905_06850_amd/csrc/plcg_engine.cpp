@@ -53,6 +53,7 @@ constexpr long long kLargeVector = 96LL << 20;   // vectors worth storing non-te
 constexpr int kResIterCap = 1 << 20;
 // Iterations one team launch may run (a few seconds at most); its tags fit an int.
 constexpr int kTeamIterCap = 1 << 20;
+constexpr int kTeamMinUnknowns = 1536;   // of a system the resident kernels take as well
 constexpr int kMaxDevices = 64;
 constexpr int kDefaultRestarts = 100;
 
@@ -444,6 +445,8 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
     return PLCG_OK;
   }
   PLCG_HIP(launch_copy(scratch, x, h->n, s));
+  // reported as the mode that AUTO has for the size
+  h->ran_resident = h->res_kind >= 0;
   *ran = true;
   return PLCG_OK;
 }
@@ -464,7 +467,7 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
   int status = kRunning;
   int group = 0;
   int last_i = -1;
-  const size_t first_launch = tl.launches();
+  size_t first_launch = tl.launches();
   plcg_status e;
   // whole: the segment runs in one launch (resident or team)
   bool whole = h->res_kind >= 0 && std::is_same<S, double>::value && m <= kResIterCap;
@@ -472,6 +475,7 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
     if (h->team && m <= kTeamIterCap) {
       if ((e = run_team(h, ring[0], x, p[1], imax, imax + 2, s, tl, &whole)) != PLCG_OK) return e;
       if (whole) last_i = 0;
+      else first_launch = tl.launches();
     } else if (whole) {
       // the whole segment in one resident launch: state copy 1 in, copy 0 out
       ResArgs ra;
@@ -762,11 +766,12 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
   };
   int group = 0;
   bool stopped = false;
-  const size_t first_launch = tl.launches();
+  size_t first_launch = tl.launches();
   bool whole = h->res_kind >= 0 && maxit <= kResIterCap;   // all iterations in one launch
   if (h->team && maxit <= kTeamIterCap) {
     if ((e = run_team(h, h->cg_r, x, h->cg_q, maxit, 2 * maxit + 4, s, tl, &whole)) != PLCG_OK)
       return e;
+    if (!whole) first_launch = tl.launches();
   } else if (whole) {
     // all iterations in one resident launch: state copy 1 in, copy 0 out
     ResArgs ra;
@@ -1244,16 +1249,25 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
     else if (cfg->launch_mode == PLCG_LAUNCH_RESIDENT)
       return fail(PLCG_E_INVALID, "PLCG_LAUNCH_RESIDENT: too many stored entries");
   }
-  // Team launches: FP64 solves of the constant stencils that AUTO would stream.  A caller
-  // who names the launch mode or the x cadence gets the sweeps that have them.
+  // Team launches: FP64 solves of the constant stencils under AUTO.  A caller who names the
+  // launch mode or the x cadence gets the kernels that have them.  Systems that the resident
+  // kernels take go to a team where a column of registers per thread beats their strided LDS
+  // reads (us per iteration, resident against team, whole solves): 64^2 p(1) 2.87 / 2.07,
+  // p(2) 2.64 / 1.90, CG 2.78 / 2.28; 70 x 68 p(2) 2.86 / 2.15; 37 x 53 p(1) 2.36 / 2.05,
+  // CG 2.37 / 2.23; 16^3 p(2) 3.72 / 3.24; but 20^2 p(2) 2.06 / 2.21, 20 x 90
+  // p(2) 2.06 / 2.40 (20 lanes of 64), 12 x 10 x 8 p(2) 2.70 / 3.38, 1 x 4000 p(2) 6.6 / 7.5, and CG over more than one workgroup 2.67 / 3.41
+  // at 100 x 37: its two sums wait for other workgroups.
   const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
   int cus = 0;
-  if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO && h->res_kind < 0 &&
+  if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO &&
       h->precision == PLCG_PREC_FP64 && stencil && !h->var && h->device >= 0 &&
       h->device < kMaxDevices &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess)
     h->team = team_plan(pl ? 1 : 0, h->l, h->d3, h->op.nx, h->op.ny, h->op.nz, cus,
-                        &h->team_geom);
+                        &h->team_geom) &&
+              (h->res_kind < 0 ||
+               (n >= kTeamMinUnknowns && h->op.nx >= (pl && h->d3 ? 16 : 32) && n / h->op.nx >= 16 &&
+                (pl || team_tiles(h->team_geom) == 1)));
   return PLCG_OK;
 }
 
@@ -1332,11 +1346,10 @@ plcg_status plcg_create(const plcg_operator_desc *op, const plcg_config *cfg, pl
   if (e == PLCG_OK && h->var) e = copy_var(h, op);
   if (e == PLCG_OK) e = finish_setup(h, op, cfg, res_ok);
   if (e == PLCG_OK && h->team) {
-    const size_t mail = team_mail_bytes(h->team_geom);
-    e = dev_alloc(h, &h->team_mail, mail);
-    if (e == PLCG_OK) e = dev_alloc(h, &h->team_post, team_post_bytes());
-    if (e == PLCG_OK && (hipMemset(h->team_mail, 0, mail) != hipSuccess ||
-                         hipMemset(h->team_post, 0, team_post_bytes()) != hipSuccess))
+    const size_t bytes = team_post_bytes() + team_mail_bytes(h->team_geom);
+    e = dev_alloc(h, &h->team_post, bytes);
+    h->team_mail = static_cast<char *>(h->team_post) + team_post_bytes();
+    if (e == PLCG_OK && hipMemsetAsync(h->team_post, 0, bytes, nullptr) != hipSuccess)
       e = fail(PLCG_E_HIP, "clearing the team mail failed");
   }
   if (e != PLCG_OK) {

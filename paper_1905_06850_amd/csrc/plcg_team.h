@@ -164,7 +164,11 @@ inline bool team_cut(int nx, int ny, int nz, int v, int tiles, TeamGeom *out) {
 //        flat once the tiles number 128 or less;
 //   CG   256^2 4.47 4.35 4.65 4.86, 512^2 - 5.04 5.04 5.38: one product per sum, so tiles
 //        cost little.
-// So: the smallest v from `lo` up to `hi` with at most `cap` tiles, else hi, else the
+// One tile is best where one workgroup holds the system: no mail (64^2 p(1) v = 5 2.07
+// against 2.28 with two tiles, 60 x 40 p(2) v = 4 1.73 against 1.92, CG v = 5 1.95 against
+// 3.06), with the most unknowns per thread that stay in registers: fewer waves share the
+// SIMDs and the barriers (37 x 53 CG v = 4 / 5 / 6 2.42 2.21 2.32, 64^2 - 2.44 2.28).
+// So: one tile if it fits with v = one (CG also 6); else the smallest v from `lo` up to `hi` with at most `cap` tiles, else hi, else the
 // smallest larger v that fits at all.  false: the system is too large (or too narrow: the
 // lanes of a wave lie along x), or its face mail would outgrow kTeamMailMax.
 inline bool team_plan(int method_plcg, int l, bool d3, int nx, int ny, int nz, int tiles,
@@ -174,6 +178,11 @@ inline bool team_plan(int method_plcg, int l, bool d3, int nx, int ny, int nz, i
   const int lo = method_plcg && l == 2 ? 3 : 2;
   const int hi = !method_plcg ? 2 : l == 3 ? 3 : 4;
   const int cap = !method_plcg ? kTeamTiles : l == 2 ? 64 : 128;
+  const int one = !method_plcg || l == 1 ? 5 : l == 2 ? 4 : 3;
+  for (int v = one; v <= vmax && v <= (method_plcg ? one : 6); ++v)
+    if (team_cut(nx, d3 ? ny : 1, d3 ? nz : ny, v, 1, out) &&
+        (v > one || method_plcg || out->wy * out->wz <= 11))
+      return true;
   for (int pass = 0; pass < 2; ++pass)
     for (int v : kTeamWidths) {
       if (v > vmax) break;

@@ -160,16 +160,21 @@ __device__ inline double products_sum(const double (&a)[ND]) {
 
 // ---- sums across the workgroups --------------------------------------------
 
-// The owner wave posts its workgroup's products of column c from the streaming
-// waves' sums.
+// The workgroup's products from the streaming waves' sums: product m in every lane
+// of row m of the owner wave.
 template <int ND>
-__device__ inline void post_products(rsrc_t post, const double (*red)[4], int nw, int c, int tile,
-                                     unsigned tag) {
+__device__ inline double own_products(const double (*red)[4], int nw) {
   const int lane = threadIdx.x & 63, k = lane & 15, row = lane >> 4;
-  const double s = row_sum(k < nw && row < ND ? red[k][row] : 0.0);
-  if (k == 0 && row < ND)
+  return row_sum(k < nw && row < ND ? red[k][row] : 0.0);
+}
+
+// The owner wave posts its workgroup's products of column c.
+template <int ND>
+__device__ inline void post_products(rsrc_t post, double own, int c, int tile, unsigned tag) {
+  const int lane = threadIdx.x & 63, row = lane >> 4;
+  if ((lane & 15) == 0 && row < ND)
     word_post(post, row * kWordBytes,
-              ((c & (kTeamRing - 1)) * kTeamTiles + tile) * kTeamProducts * kWordBytes, s, tag);
+              ((c & (kTeamRing - 1)) * kTeamTiles + tile) * kTeamProducts * kWordBytes, own, tag);
 }
 
 // Adds this lane's share of a column's posted products, PER words per lane at
@@ -212,10 +217,17 @@ __device__ inline bool share_sum(rsrc_t post, int lane_off, int off, int step, u
 // Each row of 16 lanes takes one product (one of the rows that share it, when ND <= 2)
 // and each lane of it every 16th tile of the row's share, in ascending order; then the
 // lanes are added, so every workgroup gets the same bits.  out[m] is uniform in the
-// wave.  false: lost.
+// wave.  own: this workgroup's products, which are the sum where it is alone.
+// false: lost.
 template <int ND, typename F>
-__device__ inline bool team_sum(rsrc_t post, int c, unsigned tag, int tiles, double (&out)[ND],
-                                Patience &pat, F meanwhile) {
+__device__ inline bool team_sum(rsrc_t post, int c, unsigned tag, int tiles, double own,
+                                double (&out)[ND], Patience &pat, F meanwhile) {
+  if (tiles == 1) {
+    meanwhile();
+#pragma unroll
+    for (int q = 0; q < ND; ++q) out[q] = lane_value(own, 16 * q);
+    return true;
+  }
   constexpr int G = ND == 1 ? 4 : ND == 2 ? 2 : 1;      // rows per product
   const int lane = threadIdx.x & 63, k = lane & 15, row = lane >> 4;
   const int m = G == 4 ? 0 : G == 2 ? (row & 1) : row;
@@ -491,6 +503,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
     const rsrc_t post = mail_rsrc(a.post, (int)team_post_bytes());
     double *const hist = tile == 0 ? a.hist : nullptr;
     bool running = true;
+    double own = 0.0, own_before = 0.0;   // this workgroup's products, this column's and the last's
     // column c from everybody's products; at: the sweep that a loss ends.  The entries of
     // the state it needs are gathered while the first poll travels (l = 3: before it, whose
     // words and entries together would not fit the registers).
@@ -498,7 +511,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
       EngineIn<L> in;
       double raw[ND];
       if constexpr (L >= 3) in = engine_gather<L>(sh, c);
-      if (!team_sum<ND>(post, c, base + (unsigned)c, tiles, raw, pat, [&]() {
+      if (!team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat, [&]() {
             if constexpr (L < 3) in = engine_gather<L>(sh, c);
           })) {
         if (lane == 0) lose(at);
@@ -517,7 +530,9 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
     for (; i <= a.imax; ++i) {
       pat.reset(i <= 1 + LAG);
       if (i >= 1 && running) {
-        post_products<ND>(post, red[(i - 1) & 1], nw, i, tile, base + (unsigned)i);
+        own_before = own;
+        own = own_products<ND>(red[(i - 1) & 1], nw);
+        if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
         if (i > LAG) column(i - LAG, L == 1 ? i : i + 1);
       }
       if (L == 1) __syncthreads();
@@ -525,7 +540,10 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
       __syncthreads();
     }
     // the last posted column, where it is finalised a sweep late
-    if (LAG && i > a.imax && i >= 2 && running && stop_at > i) column(a.imax, 0);
+    if (LAG && i > a.imax && i >= 2 && running && stop_at > i) {
+      own_before = own;
+      column(a.imax, 0);
+    }
   } else {
     const Place<V, D3> pl(a.g, tile, wave - 1);
     const int copy_bytes = tiles * a.g.words * kWordBytes;
@@ -758,9 +776,10 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
     const rsrc_t post = mail_rsrc(a.post, (int)team_post_bytes());
     // a reduction: column 2k is (r_k, r_k), 2k+1 is (p_k, A p_k)
     auto reduce = [&](int c) {
-      post_products<1>(post, red, nw, c, tile, base + (unsigned)c);
+      const double own = own_products<1>(red, nw);
+      if (tiles > 1) post_products<1>(post, own, c, tile, base + (unsigned)c);
       double t[1];
-      const bool ok = team_sum<1>(post, c, base + (unsigned)c, tiles, t, pat, []() {});
+      const bool ok = team_sum<1>(post, c, base + (unsigned)c, tiles, own, t, pat, []() {});
       if (lane == 0) {
         total[c & 1] = t[0];
         if (!ok) lose();
