@@ -14,6 +14,7 @@ SOURCES = [os.path.join(HERE, "csrc", "plcg_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_var_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_resident.hip"),
            os.path.join(HERE, "csrc", "plcg_team.hip"),
+           os.path.join(HERE, "csrc", "plcg_team_var.hip"),
            os.path.join(HERE, "csrc", "plcg_batch_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_noalloc.hip"),
            os.path.join(HERE, "csrc", "plcg_engine.cpp"),

@@ -423,6 +423,7 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   a.st_out = h->st[0];
   a.hs = h->hs_dev;
   a.hist = h->hist;
+  a.od = h->od;
   a.mail = h->team_mail;
   a.post = h->team_post;
   a.g = h->team_geom;
@@ -1249,7 +1250,8 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
     else if (cfg->launch_mode == PLCG_LAUNCH_RESIDENT)
       return fail(PLCG_E_INVALID, "PLCG_LAUNCH_RESIDENT: too many stored entries");
   }
-  // Team launches: FP64 solves of the constant stencils under AUTO.  A caller who names the
+  // Team launches: FP64 solves of the constant and the Jacobi-scaled variable stencils under
+  // AUTO.  A caller who names the
   // launch mode or the x cadence gets the kernels that have them.  Systems that the resident
   // kernels take go to a team where a column of registers per thread beats their strided LDS
   // reads (us per iteration, resident against team, whole solves): 64^2 p(1) 2.87 / 2.07,
@@ -1260,10 +1262,10 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
   const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
   int cus = 0;
   if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO &&
-      h->precision == PLCG_PREC_FP64 && stencil && !h->var && h->device >= 0 &&
+      h->precision == PLCG_PREC_FP64 && stencil && (!h->var || h->jacobi) && h->device >= 0 &&
       h->device < kMaxDevices &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess)
-    h->team = team_plan(pl ? 1 : 0, h->l, h->d3, h->op.nx, h->op.ny, h->op.nz, cus,
+    h->team = team_plan(pl ? 1 : 0, h->l, h->d3, h->var, h->op.nx, h->op.ny, h->op.nz, cus,
                         &h->team_geom) &&
               (h->res_kind < 0 ||
                (n >= kTeamMinUnknowns && h->op.nx >= (pl && h->d3 ? 16 : 32) && n / h->op.nx >= 16 &&

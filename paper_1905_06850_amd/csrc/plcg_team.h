@@ -99,8 +99,10 @@ struct TeamPlace {
 // Unknowns per thread the team kernels are built for: those of kTeamWidths up to this, the
 // largest that fits 128 registers (four waves per SIMD) without spilling and a CU's 160 KB
 // of LDS.
-constexpr int team_vmax(int method_plcg, int l, bool d3) {
-  return !method_plcg ? (d3 ? 5 : 10)
+// The variable-coefficient stencils' edge weights share the LDS.
+constexpr int team_vmax(int method_plcg, int l, bool d3, bool var) {
+  return var           ? (d3 ? (l == 3 ? 2 : 3) : !method_plcg ? 6 : l == 1 ? 4 : 3)
+         : !method_plcg ? (d3 ? 5 : 10)
          : l == 1     ? (d3 ? 5 : 6)
          : l == 2     ? (d3 ? 4 : 5)
          : l == 3     ? 3
@@ -171,12 +173,12 @@ inline bool team_cut(int nx, int ny, int nz, int v, int tiles, TeamGeom *out) {
 // So: one tile if it fits with v = one (CG also 6); else the smallest v from `lo` up to `hi` with at most `cap` tiles, else hi, else the
 // smallest larger v that fits at all.  false: the system is too large (or too narrow: the
 // lanes of a wave lie along x), or its face mail would outgrow kTeamMailMax.
-inline bool team_plan(int method_plcg, int l, bool d3, int nx, int ny, int nz, int tiles,
+inline bool team_plan(int method_plcg, int l, bool d3, bool var, int nx, int ny, int nz, int tiles,
                       TeamGeom *out) {
   if (tiles > kTeamTiles) tiles = kTeamTiles;
-  const int vmax = team_vmax(method_plcg, l, d3);
+  const int vmax = team_vmax(method_plcg, l, d3, var);
   const int lo = method_plcg && l == 2 ? 3 : 2;
-  const int hi = !method_plcg ? 2 : l == 3 ? 3 : 4;
+  const int want = !method_plcg ? 2 : l == 3 ? 3 : 4, hi = want < vmax ? want : vmax;
   const int cap = !method_plcg ? kTeamTiles : l == 2 ? 64 : 128;
   const int one = !method_plcg || l == 1 ? 5 : l == 2 ? 4 : 3;
   for (int v = one; v <= vmax && v <= (method_plcg ? one : 6); ++v)

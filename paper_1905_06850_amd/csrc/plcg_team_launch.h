@@ -8,7 +8,7 @@
 namespace plcg {
 
 // Team solves (plcg_team.hip): a whole segment of Alg. 1, or all of classic CG, in one
-// launch of one workgroup per tile.  Constant stencils, FP64.
+// launch of one workgroup per tile.  Constant and Jacobi-scaled variable stencils, FP64.
 struct TeamArgs {
   const double *z0;          // p(l)-CG: z_0 = u_0 / ||u_0||; CG: r_0
   const double *x;           // x at the segment start
@@ -17,6 +17,7 @@ struct TeamArgs {
   DevState *st_out;
   HostStatus *hs;
   double *hist;              // [hist_cap][4] or NULL
+  OpData od;                 // edge weights of the variable-coefficient stencil; else NULL
   void *mail, *post;         // team_mail_bytes(g), team_post_bytes()
   TeamGeom g;
   int32_t base;              // first tag of this run; tags base .. base + imax + 1 (CG: + 2 imax + 2)
@@ -24,6 +25,9 @@ struct TeamArgs {
 };
 hipError_t launch_plcg_team(const TeamArgs &a, int l, bool d3, hipStream_t s);
 hipError_t launch_cg_team(const TeamArgs &a, bool d3, hipStream_t s);
+// The same for a.od.sx != NULL (plcg_team_var.hip); the launchers above hand over to these.
+hipError_t launch_plcg_team_var(const TeamArgs &a, int l, bool d3, hipStream_t s);
+hipError_t launch_cg_team_var(const TeamArgs &a, bool d3, hipStream_t s);
 
 // A whole solve (as plcg_create + plcg_solve) in ws_bytes of device memory at
 // ws and kTeamWsBytes at team_ws, with no device or pinned host allocation; 2D and

@@ -1,7 +1,7 @@
 // Host check of the team kernels' geometry: for every case the tiles cover each
 // unknown once, every mailed word lies inside the mail, is posted by one lane and
 // read by the one whose unknown is its face neighbour, and every neighbour that lies
-// in another tile is read.  Input lines: method (1 p(l)-CG, 0 CG) l d3 nx ny nz tiles.
+// in another tile is read.  Input lines: method (1 p(l)-CG, 0 CG) l d3 var nx ny nz tiles.
 // Prints "v tiles waves words" per case, or "none" where no plan fits; exit code 1
 // on the first violation.
 #include "plcg_team.h"
@@ -19,16 +19,16 @@ static void need(bool ok, const char *what) {
 }
 
 int main() {
-  int pl, l, d3, nx, ny, nz, tiles;
-  while (std::scanf("%d %d %d %d %d %d %d", &pl, &l, &d3, &nx, &ny, &nz, &tiles) == 7) {
+  int pl, l, d3, var, nx, ny, nz, tiles;
+  while (std::scanf("%d %d %d %d %d %d %d %d", &pl, &l, &d3, &var, &nx, &ny, &nz, &tiles) == 8) {
     TeamGeom g;
-    if (!team_plan(pl, l, d3 != 0, nx, ny, nz, tiles, &g)) {
+    if (!team_plan(pl, l, d3 != 0, var != 0, nx, ny, nz, tiles, &g)) {
       std::printf("none\n");
       continue;
     }
     const int nt = team_tiles(g), nw = g.wy * g.wz, v = g.v;
     need(nt <= tiles && nt <= kTeamTiles && nw >= 1 && nw <= kTeamWaves, "tiles or waves");
-    need(v <= 32 && v <= team_vmax(pl, l, d3 != 0), "unknowns per thread");
+    need(v <= 32 && v <= team_vmax(pl, l, d3 != 0, var != 0), "unknowns per thread");
     need(team_mail_bytes(g) <= kTeamMailMax, "mail size");
     const long long size = (long long)nt * g.words * kWordBytes;
     const int n = g.nx * g.ny * g.nz;
