@@ -322,7 +322,10 @@ plcg_status plcg_solve_noalloc(const plcg_operator_desc *op, const plcg_config *
  *
  * A batch holds up to max_slots independent systems at once, each in a slot of
  * HBM sized by its footprint.  One launch ("tick") advances every system by one
- * step: setup, one p(l)-CG iteration, or the final residual and report.  A
+ * step: setup, one p(l)-CG iteration, or the final residual and report.  The
+ * iterations of an FP64 system with l = 2 or 3 whose unknowns fit the chip's registers
+ * run in launches of their own instead, many to a launch: at least one per tick asked
+ * for (not within a stream capture, where the ticks run them).  A
  * system's result does not depend on which other systems share the batch.
  * The operator of a batched system is the variable-coefficient Laplacian
  * (A u)_p = sum_q c_pq (u_p - u_q) over the grid edges incident to p (edges to
@@ -379,7 +382,8 @@ plcg_status plcg_batch_add(plcg_batch *b, const plcg_system_desc *sys, const dou
                            double *d_x, double tol, int32_t maxit, void *stream,
                            uint64_t *ticket);
 
-/* Enqueue `ticks` launches on `stream` (returns without waiting). */
+/* Enqueue what advances every system by at least `ticks` steps on `stream` (returns
+ * without waiting). */
 plcg_status plcg_batch_step(plcg_batch *b, int32_t ticks, void *stream);
 
 /* PLCG_NOT_READY until the system of `ticket` is done; then PLCG_OK with the

@@ -15,6 +15,7 @@ SOURCES = [os.path.join(HERE, "csrc", "plcg_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_resident.hip"),
            os.path.join(HERE, "csrc", "plcg_team.hip"),
            os.path.join(HERE, "csrc", "plcg_team_var.hip"),
+           os.path.join(HERE, "csrc", "plcg_team_batch.hip"),
            os.path.join(HERE, "csrc", "plcg_batch_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_noalloc.hip"),
            os.path.join(HERE, "csrc", "plcg_engine.cpp"),

@@ -9,6 +9,7 @@
 // workgroup and the slot's streaming workgroups; it is rebuilt when slots come
 // or go and uploaded on the stream, so launches already enqueued keep theirs.
 #include "plcg_internal.h"
+#include "plcg_team_launch.h"
 
 #include "../../include/plcg.h"
 
@@ -76,6 +77,23 @@ struct plcg_batch {
   std::vector<BatchState> pending_state;
   std::vector<uint64_t> pending_ticket;
   int64_t tick = 0;
+  // team launches: which systems, on which places of which launch
+  int cus = 0;                          // tiles a launch can hold; 0: no team launches
+  std::vector<TeamGeom> geom;           // per slot marked SlotDesc::team
+  struct Round {
+    int first, places, threads;         // places of the block table
+    bool d3;
+  };
+  std::vector<Round> rounds;
+  std::vector<TeamSlot> team_table;
+  std::vector<int32_t> team_blocks;
+  bool team_only = false;               // every admitted system is marked
+  int32_t *d_lost = nullptr;
+  char *d_team = nullptr;               // table, then block table
+  size_t team_cap = 0;
+  char *d_mail = nullptr;               // posted products, then the faces' mail
+  size_t mail_cap = 0;
+  int team_base = 1;                    // first tag of the next launch
   // graph of a group of ticks for the current schedule
   hipGraphExec_t gexec = nullptr;
   int graph_ticks = 0;
@@ -290,6 +308,97 @@ int batch_hint(const plcg_batch *b) {
   return bytes > ((size_t)256 << 20) ? (kHintLoads | kHintStores) : 0;
 }
 
+// Whether a system's sweeps run in team launches: where its tiles fit one, and, beyond
+// one tile, the tiles' threads are not mostly idle (lanes lie along x).  It depends on the
+// system alone, so that its result does not depend on the others.
+bool team_system(const plcg_batch *b, const SlotDesc &d, TeamGeom *g) {
+  if (b->cus < 1) return false;
+  const int v = team_slot_v(b->l, d.d3 != 0);
+  if (!team_cut(d.nx, d.d3 ? d.ny : 1, d.d3 ? d.nz : d.ny, v, b->cus, g)) return false;
+  const int64_t threads = (int64_t)team_tiles(*g) * g->wy * g->wz * 64;
+  return team_mail_bytes(*g) <= kTeamMailMax &&
+         (team_tiles(*g) == 1 || 4 * (int64_t)d.n >= threads * v);
+}
+
+// Packs the marked systems into launches of at most one tile per CU, largest first.
+void rebuild_rounds(plcg_batch *b, size_t *mail) {
+  b->rounds.clear();
+  b->team_table.clear();
+  b->team_blocks.clear();
+  b->team_only = true;
+  *mail = 0;
+  std::vector<int> order;
+  for (size_t s = 0; s < b->slots.size(); ++s)
+    if (b->in_use[s]) {
+      if (b->slots[s].team) order.push_back((int)s);
+      else b->team_only = false;
+    }
+  std::sort(order.begin(), order.end(), [&](int p, int q) {
+    const int dp = b->slots[p].d3, dq = b->slots[q].d3;
+    const int tp = team_tiles(b->geom[p]), tq = team_tiles(b->geom[q]);
+    return dp != dq ? dp < dq : tp != tq ? tp > tq : p < q;
+  });
+  size_t used = 0;                      // mail of the round
+  for (int s : order) {
+    const TeamGeom &g = b->geom[s];
+    const int tiles = team_tiles(g);
+    const size_t bytes = team_mail_bytes(g);
+    const bool d3 = b->slots[s].d3 != 0;
+    if (b->rounds.empty() || b->rounds.back().d3 != d3 ||
+        b->rounds.back().places + tiles > b->cus || used + bytes > kTeamMailMax) {
+      b->rounds.push_back(plcg_batch::Round{(int)b->team_blocks.size(), 0, 0, d3});
+      used = 0;
+    }
+    plcg_batch::Round &r = b->rounds.back();
+    TeamSlot ts{};
+    ts.g = g;
+    ts.slot = s;
+    ts.first = r.places;
+    ts.mail = (int32_t)used;
+    for (int k = 0; k < tiles; ++k) b->team_blocks.push_back((int32_t)b->team_table.size());
+    b->team_table.push_back(ts);
+    r.places += tiles;
+    r.threads = std::max(r.threads, team_threads(g));
+    used += bytes;
+    *mail = std::max(*mail, used);
+  }
+}
+
+// The team launches' tables, and their mail, on the device.  Without memory for them
+// the ticks run all sweeps.
+int32_t upload_rounds(plcg_batch *b, hipStream_t st) {
+  size_t mail = 0;
+  rebuild_rounds(b, &mail);
+  if (b->rounds.empty()) return PLCG_OK;
+  const size_t tb = b->team_table.size() * sizeof(TeamSlot), bb = b->team_blocks.size() * 4;
+  const size_t need = team_post_bytes() + mail;
+  auto none = [&]() {
+    (void)hipGetLastError();
+    b->rounds.clear();
+    return PLCG_OK;
+  };
+  if (tb + bb > b->team_cap || need > b->mail_cap) BHIP(hipStreamSynchronize(st));
+  if (tb + bb > b->team_cap) {
+    if (b->d_team) BHIP(hipFree(b->d_team));
+    b->d_team = nullptr;
+    b->team_cap = 0;
+    if (hipMalloc(reinterpret_cast<void **>(&b->d_team), 2 * (tb + bb)) != hipSuccess) return none();
+    b->team_cap = 2 * (tb + bb);
+  }
+  if (need > b->mail_cap) {
+    if (b->d_mail) BHIP(hipFree(b->d_mail));
+    b->d_mail = nullptr;
+    b->mail_cap = 0;
+    const size_t cap = std::min(team_post_bytes() + kTeamMailMax, need + mail / 2);
+    if (hipMalloc(reinterpret_cast<void **>(&b->d_mail), cap) != hipSuccess) return none();
+    b->mail_cap = cap;
+    BHIP(hipMemsetAsync(b->d_mail, 0, cap, st));
+  }
+  BHIP(hipMemcpyAsync(b->d_team, b->team_table.data(), tb, hipMemcpyHostToDevice, st));
+  BHIP(hipMemcpyAsync(b->d_team + tb, b->team_blocks.data(), bb, hipMemcpyHostToDevice, st));
+  return PLCG_OK;
+}
+
 void rebuild_schedule(plcg_batch *b) {
   b->sched.clear();
   b->hint = batch_hint(b);
@@ -302,6 +411,10 @@ void rebuild_schedule(plcg_batch *b) {
 
 int32_t upload_schedule(plcg_batch *b, hipStream_t st) {
   rebuild_schedule(b);
+  {
+    const int32_t e = upload_rounds(b, st);
+    if (e != PLCG_OK) return e;
+  }
   if (b->sched.size() > b->sched_cap) {
     // enqueued launches may still read the old table: wait for them first
     BHIP(hipStreamSynchronize(st));
@@ -320,7 +433,42 @@ int32_t upload_schedule(plcg_batch *b, hipStream_t st) {
   return PLCG_OK;
 }
 
-int32_t launch_ticks(plcg_batch *b, int ticks, hipStream_t st) {
+// One team launch per round, each of `sweeps` sweeps of its systems.
+int32_t launch_rounds(plcg_batch *b, int sweeps, hipStream_t st) {
+  const int tags = team_slot_tags(sweeps);
+  if (b->team_base > 0x7fffffff - (int64_t)tags * (int64_t)b->rounds.size()) {
+    BHIP(hipMemsetAsync(b->d_mail, 0, b->mail_cap, st));
+    b->team_base = 1;
+  }
+  TeamSlotsArgs a;
+  a.table = reinterpret_cast<const TeamSlot *>(b->d_team);
+  a.slots = b->d_slots;
+  a.state = b->d_state;
+  a.part = b->d_part;
+  a.lost = b->d_lost;
+  a.post = b->d_mail;
+  a.mail = b->d_mail + team_post_bytes();
+  a.par = (int32_t)((b->tick & 1) ^ 1);     // the copy that the next tick reads
+  a.sweeps = sweeps;
+  a.l = b->l;
+  const int32_t *blocks = reinterpret_cast<const int32_t *>(b->d_team + b->team_table.size() * sizeof(TeamSlot));
+  TeamTurn &turn = team_turn(b->device);
+  std::lock_guard<std::mutex> lk(turn.mu);
+  if (turn.last != nullptr)
+    BHIP(hipStreamWaitEvent(st, turn.last, 0));
+  else
+    BHIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
+  for (const plcg_batch::Round &r : b->rounds) {
+    a.blocks = blocks + r.first;
+    a.base = b->team_base;      // the rounds share the mail: no tag twice
+    b->team_base += tags;
+    BHIP(launch_team_slots(a, r.d3, r.places, r.threads, st));
+  }
+  BHIP(hipEventRecord(turn.last, st));
+  return PLCG_OK;
+}
+
+int32_t launch_ticks(plcg_batch *b, int ticks, hipStream_t st, bool team) {
   BatchArgs a;
   a.slots = b->d_slots;
   a.state = b->d_state;
@@ -331,6 +479,8 @@ int32_t launch_ticks(plcg_batch *b, int ticks, hipStream_t st) {
   a.l = b->l;
   a.mixed = b->mixed ? 1 : 0;
   a.hint = b->hint;
+  a.lost = b->d_lost;
+  a.team = team ? 1 : 0;
   const int grid = (int)b->sched.size();
   for (int k = 0; k < ticks; ++k) {
     a.tick = (int32_t)(b->tick & 1);
@@ -342,20 +492,11 @@ int32_t launch_ticks(plcg_batch *b, int ticks, hipStream_t st) {
 
 constexpr int kGraphTicks = 16;   // even, so a replay starts and ends on the same parity
 
-int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
-  {
-    int32_t e = flush_admissions(b, st);
-    if (e != PLCG_OK) return e;
-  }
-  if (b->dirty) {
-    int32_t e = upload_schedule(b, st);
-    if (e != PLCG_OK) return e;
-  }
-  if (b->sched.empty()) return PLCG_OK;
-  if (!b->cfg.use_graph) return launch_ticks(b, ticks, st);
+int32_t run_plain(plcg_batch *b, int ticks, hipStream_t st, bool team) {
+  if (!b->cfg.use_graph) return launch_ticks(b, ticks, st, team);
   // Replay whole groups from the graph; the remainder and parity fix-ups directly.
   if ((b->tick & 1) && ticks > 0) {
-    int32_t e = launch_ticks(b, 1, st);
+    int32_t e = launch_ticks(b, 1, st, team);
     if (e != PLCG_OK) return e;
     --ticks;
   }
@@ -365,7 +506,7 @@ int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
     hipGraph_t g;
     int64_t saved = b->tick;
     hipError_t he = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-    int32_t e = he == hipSuccess ? launch_ticks(b, kGraphTicks, cap) : PLCG_E_HIP;
+    int32_t e = he == hipSuccess ? launch_ticks(b, kGraphTicks, cap, !b->rounds.empty()) : PLCG_E_HIP;
     hipError_t he2 = hipStreamEndCapture(cap, &g);
     b->tick = saved;
     (void)hipStreamDestroy(cap);
@@ -379,7 +520,47 @@ int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
     b->tick += kGraphTicks;
     ticks -= kGraphTicks;
   }
-  return launch_ticks(b, ticks, st);
+  return launch_ticks(b, ticks, st, team);
+}
+
+// Team launches go ahead of the ticks, for kTeamTicks ticks at most at a time (other team
+// launches wait meanwhile).  Where all systems are swept there, the ticks only do the
+// setup (four phases) and the report (three) of a solve.  A caller of a few ticks wants to
+// look again soon and gets a sweep for each; a whole group is worth kTeamSweeps for
+// each, as loading and storing the vectors, the ticks and the wait (40 us together) would
+// else take as long as the sweeps.  A burst of 24 systems of 32^2 .. 256^2 unknowns, p(2),
+// served 16 ticks at a time: 22.9 ms by ticks alone, 5.9, 4.3, 3.5, 3.1 ms with 1, 2, 4, 8
+// sweeps per tick; with 4 a group still takes less than its ticks did (215 us, 320).
+constexpr int kTeamSweeps = 4, kTeamTicks = 16, kTeamSetup = 4;
+
+int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
+  {
+    int32_t e = flush_admissions(b, st);
+    if (e != PLCG_OK) return e;
+  }
+  if (b->dirty) {
+    int32_t e = upload_schedule(b, st);
+    if (e != PLCG_OK) return e;
+  }
+  if (b->sched.empty()) return PLCG_OK;
+  if (!b->rounds.empty()) {
+    // In a caller's capture the ticks run all sweeps: a replayed launch's tags would
+    // not be new, and nothing would keep it apart from other team launches.
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return run_plain(b, ticks, st, false);
+    }
+    while (ticks > 0) {
+      const int t = std::min(ticks, kTeamTicks);
+      int32_t e = launch_rounds(b, t < kTeamTicks ? t : kTeamSweeps * t, st);
+      if (e == PLCG_OK) e = run_plain(b, b->team_only ? std::min(t, kTeamSetup) : t, st, true);
+      if (e != PLCG_OK) return e;
+      ticks -= t;
+    }
+    return PLCG_OK;
+  }
+  return run_plain(b, ticks, st, false);
 }
 
 }  // namespace
@@ -426,6 +607,7 @@ plcg_status plcg_batch_create(const plcg_batch_config *cfg, plcg_batch **out) {
     if (b->d_state) (void)hipFree(b->d_state);
     if (b->d_part) (void)hipFree(b->d_part);
     if (b->d_tickets) (void)hipFree(b->d_tickets);
+    if (b->d_lost) (void)hipFree(b->d_lost);
     if (b->reports) (void)hipHostFree(b->reports);
     delete b;
     return set_last_error(PLCG_E_NOMEM, m.c_str());
@@ -444,6 +626,16 @@ plcg_status plcg_batch_create(const plcg_batch_config *cfg, plcg_batch **out) {
     return bad("hipMalloc(partials)", e);
   if ((e = hipMalloc(reinterpret_cast<void **>(&b->d_tickets), sizeof(uint64_t) * S)) != hipSuccess)
     return bad("hipMalloc(tickets)", e);
+  if ((e = hipMalloc(reinterpret_cast<void **>(&b->d_lost), sizeof(int32_t) * S)) != hipSuccess ||
+      (e = hipMemset(b->d_lost, 0, sizeof(int32_t) * S)) != hipSuccess)
+    return bad("hipMalloc(lost)", e);
+  b->geom.assign(S, TeamGeom{});
+  if (!b->mixed && b->l <= kTeamLMax && b->device < kMaxDevices) {
+    if ((e = hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, b->device)) !=
+        hipSuccess)
+      return bad("hipDeviceGetAttribute", e);
+    b->cus = std::min(b->cus, kTeamTiles);
+  }
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&b->reports), sizeof(SlotReport) * S,
                          hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
     return bad("hipHostMalloc(reports)", e);
@@ -520,6 +712,7 @@ int32_t admit(plcg_batch *b, const plcg_system_desc *sys, const Layout &L, bool 
   sd.mixed = b->mixed ? 1 : 0;
   sd.tol = tol;
   sd.inner_tol = b->inner_tol;
+  sd.team = team_system(b, sd, &b->geom[slot]) ? 1 : 0;
   BatchState bs;
   std::memset(&bs, 0, sizeof(bs));
   bs.d.l = b->l;
@@ -795,6 +988,9 @@ plcg_status plcg_batch_destroy(plcg_batch *b) {
   if (b->d_part) (void)hipFree(b->d_part);
   if (b->d_sched) (void)hipFree(b->d_sched);
   if (b->d_tickets) (void)hipFree(b->d_tickets);
+  if (b->d_lost) (void)hipFree(b->d_lost);
+  if (b->d_team) (void)hipFree(b->d_team);
+  if (b->d_mail) (void)hipFree(b->d_mail);
   if (b->reports) (void)hipHostFree(b->reports);
   delete b;
   return PLCG_OK;

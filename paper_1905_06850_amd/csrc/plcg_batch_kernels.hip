@@ -19,6 +19,7 @@
 // correction c) in FP32 and keep y, the residual, the operator and every scalar
 // in FP64: each refinement step recomputes r = D^{-1/2} b - A~ y, solves
 // A~ c = r with the FP32-stored p(l)-CG to inner_tol ||r||, and adds y += c.
+#include "plcg_batch_phase.h"
 #include "plcg_device.h"
 
 #include <type_traits>
@@ -76,20 +77,44 @@ __device__ inline void slot_sweep_args(const SlotDesc &S, int i, SweepArgsT<T> &
   a.n = S.n;
 }
 
+// Whether the slot is in sweeps that team launches run.  One whose stop is known has at
+// most l sweeps left, which a tick may find here after ticks without team launches.
+__device__ inline bool team_sweeps_slot(const BatchArgs &a, const SlotDesc &S,
+                                        const BatchState &b) {
+  return a.team != 0 && S.team != 0 && b.solo == 0 && b.phase == kSweep &&
+         b.d.status == kRunning;
+}
+
 // Owner step: carry the state, run the slot's scalar work, pick the next phase.
 template <int L>
 __device__ void owner_step(const BatchArgs &a, int slot, const SlotDesc &S, const BatchState *in,
                            BatchState *out, const double *part_in, BatchState *sh, double *lds,
                            double *red) {
   constexpr int ND = L + 1;
+  const int lost = a.lost[slot];
   bstate_load(in, sh);
   const int phase = sh->phase;
+  // Sweeps that run in team launches: the state goes on as it is.
+  if (lost == 0 && team_sweeps_slot(a, S, *sh)) {
+    bstate_store(sh, out);
+    return;
+  }
   if (phase == kStart || (phase == kSweep && sh->i >= 1 && sh->d.status == kRunning) ||
-      phase == kFinal2)
-    sum_partials<ND>(part_in, sh->nparts, kMaxStream, lds, red);
+      phase == kFinal2) {
+    if (sh->nparts > 0)
+      sum_partials<ND>(part_in, sh->nparts, kMaxStream, lds, red);
+    else if (threadIdx.x == 0)
+      for (int m = 0; m < ND && m < 4; ++m) red[m] = sh->raw[m];
+  }
   if (threadIdx.x == 0) {
     BatchState &b = *sh;
-    switch (phase) {
+    // A lost team launch may have stored some tiles' x_t and not others': the
+    // solve starts again from what x holds, and its ticks run the sweeps.
+    if (lost != 0) {
+      a.lost[slot] = 0;
+      b.solo = 1;
+      b.phase = kResid;
+    } else switch (phase) {
       case kInit:
         b.phase = kResid;
         break;
@@ -148,40 +173,7 @@ __device__ void owner_step(const BatchArgs &a, int slot, const SlotDesc &S, cons
         DevState &d = b.d;
         const int i = b.i;
         if (i >= 1 && d.status == kRunning) engine_column_l<L>(d, red, i, nullptr);
-        // The next sweep has t' = i + 1 - l; stop once nothing is left to do.
-        // FP32-refined: every end of the inner solve adds its correction
-        // (kCorrect) and returns to the FP64 residual, where kStart decides.
-        const int tn = i + 1 - L;
-        const int done = S.mixed ? kCorrect : kFinal;
-        int next = kSweep;
-        if (d.status == kRunning) {
-          if (tn > b.m) {
-            b.total += b.m;
-            b.reason = 2;
-            next = done;
-          }
-        } else if (tn > d.last_t) {
-          if (d.status == kConverged) {
-            const int td = d.last_t < b.m ? d.last_t : b.m;
-            b.total += td;
-            b.reason = d.last_t <= b.m ? 1 : 2;
-            next = done;
-          } else {  // breakdown: restart from x_{t-1} (Sec. 2.2), keeping the reference norm
-            b.total += d.last_t > 0 ? (d.last_t < b.m ? d.last_t : b.m) : 0;
-            b.restarts += 1;
-            if (b.restarts > S.max_restarts) {
-              b.reason = 3;
-              next = done;
-            } else if (b.total >= S.maxit) {
-              b.reason = 2;
-              next = done;
-            } else {
-              next = S.mixed ? kCorrect : kResid;
-            }
-          }
-        }
-        b.phase = next;
-        b.i = i + 1;
+        sweep_next<L>(b, d, S, i);
         break;
       }
       case kCorrect:
@@ -246,6 +238,7 @@ __global__ __launch_bounds__(kThreads) void batch_tick_kernel(BatchArgs a) {
   }
   const int phase = in->phase;
   if (phase == kEmpty || phase == kDone || phase == kStart || phase == kReport) return;
+  if (team_sweeps_slot(a, S, *in)) return;
   const VarOp op{S.sx, S.sy, S.sz, S.n, S.nx, S.ny, S.nz, S.d3, nullptr};
   double acc[ND];
 #pragma unroll

@@ -29,6 +29,16 @@
 
 using namespace plcg;
 
+namespace plcg {
+
+// Never destroyed: a solve may still run in another thread when the process ends.
+TeamTurn &team_turn(int device) {
+  static TeamTurn *const turns = new TeamTurn[kMaxDevices];
+  return turns[device];
+}
+
+}  // namespace plcg
+
 namespace {
 
 thread_local std::string g_last_error;
@@ -54,13 +64,7 @@ constexpr int kResIterCap = 1 << 20;
 // Iterations one team launch may run (a few seconds at most); its tags fit an int.
 constexpr int kTeamIterCap = 1 << 20;
 constexpr int kTeamMinUnknowns = 1536;   // of a system the resident kernels take as well
-constexpr int kMaxDevices = 64;
 constexpr int kDefaultRestarts = 100;
-
-// A team launch needs all its workgroups on the GPU at once, so two of them at a time
-// would wait for each other: one runs on a device at a time (within the process;
-// across processes the kernel's bounded waits and the streaming sweeps take over).
-std::mutex g_team_mu[kMaxDevices];
 
 // Streaming cache hints for the sweeps of a solver whose vectors are `word`
 // bytes per unknown (measured on 2048^2 and 256^3 Poisson, the 2048^2 CSR
@@ -431,7 +435,9 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   a.imax = imax;
   h->team_base += tags;
   plcg_status e;
-  std::lock_guard<std::mutex> lk(g_team_mu[h->device]);
+  TeamTurn &turn = team_turn(h->device);
+  std::lock_guard<std::mutex> lk(turn.mu);
+  if (turn.last != nullptr) PLCG_HIP(hipStreamWaitEvent(s, turn.last, 0));
   if ((e = tl.begin_group()) != PLCG_OK) return e;
   if (h->method == PLCG_METHOD_CG)
     PLCG_HIP(launch_cg_team(a, h->d3, s));

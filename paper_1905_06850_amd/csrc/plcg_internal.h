@@ -262,12 +262,14 @@ struct BatchState {
   int32_t total;      // x-updates over all segments
   int32_t reason;     // PLCG_REASON_* once done
   int32_t first;      // 1 until the first segment has started
-  int32_t nparts;     // streaming blocks of the previous tick (partials written)
+  int32_t nparts;     // streaming blocks of the previous tick (partials written); 0: the
+                      // products of sweep i-1 are in raw (left by a team launch)
   int32_t outer;      // FP32-refined: refinement steps (corrections added)
-  int32_t pad2;
+  int32_t solo;       // a team launch lost this system: its ticks run its sweeps
   double rref_orig;   // ||b - A x0|| in the original (unscaled) norm
   double res_scaled;  // final ||r~|| / ||r~_0||
   double res_orig;    // final ||b - A x|| / ||b - A x0||
+  double raw[4];
 };
 
 // Per slot, written by the host at admission.
@@ -280,6 +282,7 @@ struct SlotDesc {
   int64_t vstride;
   int32_t nx, ny, nz, d3, n, nchunks, nblocks, maxit;
   int32_t max_restarts, mixed;         // mixed: FP32-refined
+  int32_t team, pad;                    // sweeps run in team launches
   double tol;
   double inner_tol;                     // FP32-refined inner stop, relative to ||r_k||
 };
@@ -302,6 +305,8 @@ struct BatchArgs {
   int32_t tick, l;
   int32_t mixed;           // FP32-refined batch: vectors stored in FP32
   int32_t hint;            // streaming cache hints of the sweep phase (kHint* bits)
+  int32_t *lost;           // per slot, not 0: a team launch ended without all its workgroups
+  int32_t team;            // 1: team launches run the sweeps of the slots marked for them
 };
 
 hipError_t launch_batch_tick(const BatchArgs &a, int blocks, hipStream_t s);

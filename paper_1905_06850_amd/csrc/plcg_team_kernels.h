@@ -74,7 +74,7 @@ __device__ inline void fresh() { asm volatile("" ::: "memory"); }
 
 // The time limit of a wait, and what ends it early: another workgroup's loss.
 struct Patience {
-  HostStatus *hs;
+  int32_t *lost;
   int base;
   long long t0, limit;
   int spins;
@@ -91,7 +91,7 @@ struct Patience {
       return false;
     }
     return now - t0 > limit ||
-           __hip_atomic_load(&hs->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == base;
+           __hip_atomic_load(lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == base;
   }
 };
 
@@ -250,16 +250,20 @@ __device__ inline bool team_sum(rsrc_t post, int c, unsigned tag, int tiles, dou
     const int per = left < 128 * G ? (left + 16 * G - 1) / (16 * G) : 8;
     const bool has = m < ND && t0 + first < tiles;
     const bool last = m < ND && t0 + first + 16 * G * (per - 1) < tiles;
+    // (every chunk is polled, lost or not: with `ok && share_sum` the compiler left ok
+    // undefined on one of the cases' paths)
+    bool got;
     switch (per) {
-      case 1: ok = ok && share_sum<1>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 2: ok = ok && share_sum<2>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 3: ok = ok && share_sum<3>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 4: ok = ok && share_sum<4>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 5: ok = ok && share_sum<5>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 6: ok = ok && share_sum<6>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 7: ok = ok && share_sum<7>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      default: ok = ok && share_sum<8>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 1: got = share_sum<1>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 2: got = share_sum<2>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 3: got = share_sum<3>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 4: got = share_sum<4>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 5: got = share_sum<5>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 6: got = share_sum<6>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      case 7: got = share_sum<7>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
+      default: got = share_sum<8>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
     }
+    ok = ok & got;
   }
   s = row_sum(s);
   if constexpr (G == 4) s = swap_add<16>(s, s);
@@ -535,13 +539,19 @@ __device__ inline void halo_add(const Place<V, D3> &pl, const Edges<V, D3, VAR> 
 // Within a sweep the faces are requested first, everything that does not need
 // A z_i (bases, p, x) is computed while they travel (l >= 2), and z_{i+1}'s faces
 // are posted before the products are formed.
-template <int L, int V, bool D3, bool VAR>
-__global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamArgs a) {
+//
+// RUN is WholeRun, or SlotRun for the sweeps of a batched system: those from i0 on to
+// iend, or to the stop if that is known by then, from the slot's vectors and state and back.
+template <int L, int V, bool D3, bool VAR, typename RUN>
+__device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   constexpr int ND = L + 1;
   constexpr int R = L - 1 > 2 ? L - 1 : 2;
-  constexpr int LAG = L >= 3 ? 1 : 0;
+  constexpr bool SLOT = RUN::kSlot;
+  constexpr int LAG = L >= 3 && !SLOT ? 1 : 0;
   constexpr int SR = shared_rows<V, D3>();
-  constexpr bool XL = team_x_in_lds(L, V, D3), PL = team_p_in_lds(L, V, D3);
+  // (also a batched system's x at l = 3, for the registers)
+  constexpr bool XL = team_x_in_lds(L, V, D3) || (SLOT && L == 3 && !D3);
+  constexpr bool PL = team_p_in_lds(L, V, D3);
   constexpr int NT = kTeamWaves * 64;
   __shared__ double rows[2][kTeamWaves][SR][64];   // z^{(l)}_i rows by sweep parity
   __shared__ double xs[XL ? V : 1][XL ? NT : 1], ps[PL ? V : 1][PL ? NT : 1];
@@ -553,30 +563,43 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
   // sweep's look at it, to a later sweep than any that a wave may be about to look
   // for, so all waves (and, from the same products, all workgroups) leave together.
   __shared__ int stop_at;
+  __shared__ int gone;                             // SLOT: this workgroup lost the run
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = (blockDim.x >> 6) - 1;
-  const int tile = blockIdx.x, tiles = gridDim.x;
-  const unsigned base = (unsigned)a.base;
-  Patience pat{a.hs, a.base, 0, 0, 0};
+  const int nw = SLOT ? a.g.wy * a.g.wz : (blockDim.x >> 6) - 1;
+  const int tile = run.tile(), tiles = SLOT ? team_tiles(a.g) : gridDim.x;
+  const int i0 = run.first();
+  const unsigned base = (unsigned)(a.base - i0);   // the tag of sweep i is base + i
+  int32_t *const lost = run.lost(a);
+  Patience pat{lost, a.base, 0, 0, 0};
 
   state_copy(a.st_in, &sh);
-  if (threadIdx.x == 0) stop_at = kNever;
+  if (threadIdx.x == 0) {
+    stop_at = kNever;
+    if constexpr (SLOT) gone = 0;
+  }
   __syncthreads();
   auto lose = [&](int at) {
     atomicMin(&stop_at, at);
-    __hip_atomic_store(&a.hs->lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if constexpr (SLOT) gone = 1;
+    __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  // Whether sweep i does not run.  A batched system's launch ends after sweep iend, but
+  // not between the column that stops the solve and its last sweep.
+  auto ended = [&](int i) {
+    const int at = stop_at;
+    return at <= i || (SLOT && i > a.imax && at == kNever);
   };
 
   if (wave == 0) {
-    const rsrc_t post = mail_rsrc(a.post, (int)team_post_bytes());
+    const rsrc_t post = mail_rsrc(a.post, (int)(team_post_bytes() - run.post_offset()));
     double *const hist = tile == 0 ? a.hist : nullptr;
     bool running = true;
     double own = 0.0, own_before = 0.0;   // this workgroup's products, this column's and the last's
     // column c from everybody's products; at: the sweep that a loss ends.  The entries of
     // the state it needs are gathered while the first poll travels (l = 3: before it, whose
     // words and entries together would not fit the registers).
-    auto column = [&](int c, int at) {
+    auto column = [&](int c, int at, bool over) {
       EngineIn<L> in;
       double raw[ND];
       if constexpr (L >= 3) in = engine_gather<L>(sh, c);
@@ -585,7 +608,12 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
           })) {
         if (lane == 0) lose(at);
         running = false;
-      } else {
+        return;
+      }
+      if constexpr (SLOT) {
+        if (over) run.template leave<L>(sh, c, raw);
+      }
+      if (!over) {
         if (lane == 0) {
           coef[(c - 1) & 3] = engine_step<L>(sh, in, raw, c, hist);
           // the stop: x_{last_t} is formed by sweep last_t + L
@@ -594,25 +622,46 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
         running = __builtin_amdgcn_readfirstlane(sh.status) == kRunning;
       }
     };
+    if constexpr (SLOT) {
+      run.template resume<L>(sh, coef);
+      if (i0 >= 1) {
+        double raw[ND];
+        run.template pending<ND>(raw);
+        if (lane == 0) {
+          coef[(i0 - 1) & 3] = engine_step<L>(sh, engine_gather<L>(sh, i0), raw, i0, nullptr);
+          if (sh.status != kRunning) stop_at = sh.last_t + L + 1;
+        }
+        running = __builtin_amdgcn_readfirstlane(sh.status) == kRunning;
+      }
+    }
     __syncthreads();
-    int i = 0;
-    for (; i <= a.imax; ++i) {
-      pat.reset(i <= 1 + LAG);
-      if (i >= 1 && running) {
+    int i = i0;
+    for (; SLOT || i <= a.imax; ++i) {
+      // SLOT, over: everybody posts the products of the last sweep, of which the next
+      // launch makes column i, and tile 0 collects them, so that it rewrites the state
+      // only after all the others have read it.
+      const bool over = SLOT && ended(i);
+      pat.reset(i - i0 <= 1 + LAG);
+      if (i >= (SLOT ? i0 + 1 : 1) && (running || (over && !gone))) {
         own_before = own;
         own = own_products<ND>(red[(i - 1) & 1], nw);
         if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
-        if (i > LAG) column(i - LAG, L == 1 ? i : i + 1);
+        if (i > LAG && (!over || tile == 0)) column(i - LAG, L == 1 ? i : i + 1, over);
       }
+      if (SLOT && over) break;
       if (L == 1) __syncthreads();
-      if (stop_at <= i) break;
+      if (!SLOT && stop_at <= i) break;
       __syncthreads();
     }
     // the last posted column, where it is finalised a sweep late
     if (LAG && i > a.imax && i >= 2 && running && stop_at > i) {
       own_before = own;
-      column(a.imax, 0);
+      column(a.imax, 0, false);
     }
+  } else if (SLOT && wave > nw) {
+    // waves that this system does not need keep the barriers
+    __syncthreads();
+    for (int i = i0; !ended(i); ++i) __syncthreads();
   } else {
     const Place<V, D3> pl(a.g, tile, wave - 1);
     const int copy_bytes = tiles * a.g.words * kWordBytes;
@@ -631,32 +680,39 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
     double sig[L];
 #pragma unroll
     for (int k = 0; k < L; ++k) sig[k] = lane_value(sh.sigma[k], 0);
+    if constexpr (SLOT) {
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      const double z0 = pl.in(v) ? a.z0[pl.p0 + v * pl.stride] : 0.0;
+      for (int v = 0; v < V; ++v)
+        run.template load<L, R>(pl.in(v), pl.p0 + v * pl.stride, zl, zk, p(v), x(v), v);
+    } else {
 #pragma unroll
-      for (int h = 0; h < R; ++h) zl[h][v] = h == 0 ? z0 : 0.0;
+      for (int v = 0; v < V; ++v) {
+        const double z0 = pl.in(v) ? a.z0[pl.p0 + v * pl.stride] : 0.0;
 #pragma unroll
-      for (int k = 0; k < L; ++k) {
-        zk[k][0][v] = k == 0 ? z0 : 0.0;
-        zk[k][1][v] = 0.0;
+        for (int h = 0; h < R; ++h) zl[h][v] = h == 0 ? z0 : 0.0;
+#pragma unroll
+        for (int k = 0; k < L; ++k) {
+          zk[k][0][v] = k == 0 ? z0 : 0.0;
+          zk[k][1][v] = 0.0;
+        }
+        p(v) = 0.0;
+        x(v) = pl.in(v) ? a.x[pl.p0 + v * pl.stride] : 0.0;
       }
-      p(v) = 0.0;
-      x(v) = pl.in(v) ? a.x[pl.p0 + v * pl.stride] : 0.0;
     }
     edges.load(a.od, pl, a.g);
-    halo_post<V, D3>(mail, pl, 0, base, zl[0]);
-    rows_put<V, D3, SR>(rows[0], pl, zl[0]);
+    halo_post<V, D3>(mail, pl, (i0 & 1) * copy_bytes, base + (unsigned)i0, zl[0]);
+    rows_put<V, D3, SR>(rows[i0 & 1], pl, zl[0]);
     __syncthreads();
-    for (int i = 0; i <= a.imax; ++i) {
+    int i = i0;
+    for (; SLOT || i <= a.imax; ++i) {
       const int t = i - L;
       const int copy = (i & 1) * copy_bytes, copy_next = copy_bytes - copy;
       const unsigned tag = base + (unsigned)i;
       SweepCoef cf;
       HaloWords hw;
       double s[V];
-      if (L >= 2 && stop_at <= i) break;
-      pat.reset(i <= 1);
+      if (L >= 2 && ended(i)) break;
+      pat.reset(i - i0 <= 1);
       halo_request<V, D3>(mail, pl, copy, hw);
       // neighbour sums of z_i, from the wave, the workgroup and the mail
       auto neighbours = [&]() {
@@ -762,16 +818,41 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
       if ((lane & 15) == 0 && (lane >> 4) < ND) red[i & 1][wave - 1][lane >> 4] = q;
       __syncthreads();
     }
+    if constexpr (SLOT) {
+      if (!gone) {
+        const bool over = stop_at <= i || i - L > run.m;
 #pragma unroll
-    for (int v = 0; v < V; ++v)
-      if (pl.in(v)) a.x_out[pl.p0 + v * pl.stride] = x(v);
+        for (int v = 0; v < V; ++v)
+          if (pl.in(v))
+            run.template store<L, R>(i, over, pl.p0 + v * pl.stride, zl, zk, p(v), x(v), v);
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (pl.in(v)) a.x_out[pl.p0 + v * pl.stride] = x(v);
+    }
   }
+  if constexpr (SLOT) return;
   __syncthreads();
   if (tile == 0) {
     state_copy(&sh, a.st_out);
     if (threadIdx.x == 0)
       publish(sh, a.hs, sh.cols >= 1 ? fabs(sh.zeta[(sh.cols - 1) % kTRing]) : sh.beta, sh.cols);
   }
+}
+
+// A whole segment of a solve: the launch's workgroups are the system's tiles.
+struct WholeRun {
+  static constexpr bool kSlot = false;
+  __device__ inline int tile() const { return blockIdx.x; }
+  __device__ inline int first() const { return 0; }
+  __device__ inline int post_offset() const { return 0; }
+  __device__ inline int32_t *lost(const TeamArgs &a) const { return &a.hs->lost; }
+};
+
+template <int L, int V, bool D3, bool VAR>
+__global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamArgs a) {
+  team_sweeps<L, V, D3, VAR>(a, WholeRun{});
 }
 
 // Classic CG (Sec. 2.1), iterations k = 0 .. imax - 1 and the stopping test of
@@ -804,7 +885,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   const int nw = (blockDim.x >> 6) - 1;
   const int tile = blockIdx.x, tiles = gridDim.x;
   const unsigned base = (unsigned)a.base;
-  Patience pat{a.hs, a.base, 0, 0, 0};
+  Patience pat{&a.hs->lost, a.base, 0, 0, 0};
 
   state_copy(a.st_in, &sh);
   if (threadIdx.x == 0) lost = 0;

@@ -2,6 +2,8 @@
 // its mail.
 #pragma once
 
+#include <mutex>
+
 #include "plcg_internal.h"
 #include "plcg_team.h"
 
@@ -28,6 +30,45 @@ hipError_t launch_cg_team(const TeamArgs &a, bool d3, hipStream_t s);
 // The same for a.od.sx != NULL (plcg_team_var.hip); the launchers above hand over to these.
 hipError_t launch_plcg_team_var(const TeamArgs &a, int l, bool d3, hipStream_t s);
 hipError_t launch_cg_team_var(const TeamArgs &a, bool d3, hipStream_t s);
+
+// A batched system's tiles in a team launch of several systems.
+struct TeamSlot {
+  TeamGeom g;
+  int32_t slot, first;       // slot of the batch; its tile 0's place in the launch
+  int32_t mail;              // its faces' mail: byte offset
+  int32_t pad;
+};
+
+// Sweeps of all the systems of one launch (plcg_team_batch.hip): those of the
+// Jacobi-scaled variable-coefficient operator, FP64, l = 2 or 3.
+struct TeamSlotsArgs {
+  const TeamSlot *table;
+  const int32_t *blocks;     // per place: entry of the table, or -1
+  const SlotDesc *slots;
+  BatchState *state;         // as BatchArgs, copy `par` is read and rewritten
+  const double *part;
+  int32_t *lost;
+  char *mail, *post;
+  int32_t par, base, sweeps, l;
+};
+// Unknowns per thread of those kernels.
+constexpr int team_slot_v(int l, bool d3) { return team_vmax(1, l, d3, true); }
+// Tags that a launch of `sweeps` sweeps uses at most.
+constexpr int team_slot_tags(int sweeps) { return sweeps + 2 * kTeamLMax + 2; }
+hipError_t launch_team_slots(const TeamSlotsArgs &a, bool d3, int places, int threads,
+                             hipStream_t s);
+
+// A team launch needs all its workgroups on the GPU at once, so two of them at a time would
+// wait for each other: one runs on a device at a time (within the process; across
+// processes the kernels' bounded waits and the streaming sweeps take over).  Solves, which
+// wait for their launch, hold `mu` meanwhile; launches that are only enqueued hold it while
+// they are, wait for `last` and record it.
+struct TeamTurn {
+  std::mutex mu;
+  hipEvent_t last = nullptr;
+};
+constexpr int kMaxDevices = 64;
+TeamTurn &team_turn(int device);
 
 // A whole solve (as plcg_create + plcg_solve) in ws_bytes of device memory at
 // ws and kTeamWsBytes at team_ws, with no device or pinned host allocation; 2D and
