@@ -78,6 +78,7 @@ struct Patience {
   int base;
   long long t0, limit;
   int spins;
+  bool gone;                     // a sum was given up
   __device__ inline void reset(bool start) {
     spins = 0;
     limit = start ? kStartTicks : kWaitTicks;
@@ -183,15 +184,19 @@ __device__ inline void post_products(rsrc_t post, double own, int c, int tile, u
 // lane_off + off, off + step, ..., to s in this order.  They are polled in rounds: those
 // that have not arrived are requested again, all of a round's requests in flight
 // together (one after the other, the words of 256 workgroups took 3.9 us).  Only the
-// last word of a lane may be missing from the share.  meanwhile() is run once, while the
-// first round travels.  false: lost.
+// last word of a lane may be missing from the share (apart > 0: those of the lane's words
+// that lie beyond `left` are).  meanwhile() is run once, while the first round travels.
+// pat.gone: lost.  (Kept there, as of a result `ok && share_sum(...)` over the cases
+// below the compiler left ok undefined on the path of one case.)
 template <int PER, typename F>
-__device__ inline bool share_sum(rsrc_t post, int lane_off, int off, int step, unsigned tag,
-                                 bool has, bool last, double &s, Patience &pat, F meanwhile) {
+__device__ inline void share_sum(rsrc_t post, int lane_off, int off, int step, unsigned tag,
+                                 bool has, bool last, double &s, Patience &pat, F meanwhile,
+                                 int left = 0, int apart = 0) {
   word4 w[PER];
-  bool miss[PER];
+  bool miss[PER], mine[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) miss[j] = j < PER - 1 ? has : last;
+  for (int j = 0; j < PER; ++j)
+    miss[j] = mine[j] = apart > 0 ? has && left > j * apart : j < PER - 1 ? has : last;
   bool first = true;
   while (true) {
     fresh();
@@ -207,12 +212,14 @@ __device__ inline bool share_sum(rsrc_t post, int lane_off, int off, int step, u
       any = any || miss[j];
     }
     if (!__any(any)) break;
-    if (pat.over()) return false;
+    if (pat.over()) {
+      pat.gone = true;
+      return;
+    }
   }
 #pragma unroll
   for (int j = 0; j < PER; ++j)
-    if (j < PER - 1 ? has : last) s += word_value(w[j]);
-  return true;
+    if (mine[j]) s += word_value(w[j]);
 }
 
 // The owner wave's sum of the posted products of column c over all workgroups.
@@ -237,40 +244,33 @@ __device__ inline bool team_sum(rsrc_t post, int c, unsigned tag, int tiles, dou
   const int line = kTeamProducts * kWordBytes, step = 16 * G * line;
   const int lane_off = first * line + m * kWordBytes;
   int off = (c & (kTeamRing - 1)) * kTeamTiles * line;
-  bool ok = true;
   double s = 0.0;
-  bool done = false;
-  auto todo = [&]() {
-    if (!done) meanwhile();
-    done = true;
-  };
   // up to eight words per lane at a time (their registers)
-  for (int t0 = 0; t0 < tiles; t0 += 128 * G, off += 8 * step) {
-    const int left = tiles - t0;
-    const int per = left < 128 * G ? (left + 16 * G - 1) / (16 * G) : 8;
-    const bool has = m < ND && t0 + first < tiles;
-    const bool last = m < ND && t0 + first + 16 * G * (per - 1) < tiles;
-    // (every chunk is polled, lost or not: with `ok && share_sum` the compiler left ok
-    // undefined on one of the cases' paths)
-    bool got;
-    switch (per) {
-      case 1: got = share_sum<1>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 2: got = share_sum<2>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 3: got = share_sum<3>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 4: got = share_sum<4>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 5: got = share_sum<5>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 6: got = share_sum<6>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      case 7: got = share_sum<7>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-      default: got = share_sum<8>(post, lane_off, off, step, tag, has, last, s, pat, todo); break;
-    }
-    ok = ok & got;
+  const int per = tiles < 128 * G ? (tiles + 16 * G - 1) / (16 * G) : 8;
+  const bool has = m < ND && first < tiles;
+  const bool last = m < ND && first + 16 * G * (per - 1) < tiles;
+  switch (per) {
+    case 1: share_sum<1>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    case 2: share_sum<2>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    case 3: share_sum<3>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    case 4: share_sum<4>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    case 5: share_sum<5>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    case 6: share_sum<6>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    case 7: share_sum<7>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+    default: share_sum<8>(post, lane_off, off, step, tag, has, last, s, pat, meanwhile); break;
+  }
+  // beyond 128 G tiles, four words at a time
+  for (int t0 = 128 * G; t0 < tiles; t0 += 64 * G) {
+    off += (t0 == 128 * G ? 8 : 4) * step;
+    const int left = tiles - t0 - first;
+    share_sum<4>(post, lane_off, off, step, tag, m < ND && left > 0, false, s, pat, []() {}, left, 16 * G);
   }
   s = row_sum(s);
   if constexpr (G == 4) s = swap_add<16>(s, s);
   if constexpr (G >= 2) s = swap_add<32>(s, s);
 #pragma unroll
   for (int q = 0; q < ND; ++q) out[q] = lane_value(s, 16 * q);
-  return ok;
+  return !pat.gone;
 }
 
 __device__ inline void state_copy(const DevState *src, DevState *dst) {
@@ -571,7 +571,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   const int i0 = run.first();
   const unsigned base = (unsigned)(a.base - i0);   // the tag of sweep i is base + i
   int32_t *const lost = run.lost(a);
-  Patience pat{lost, a.base, 0, 0, 0};
+  Patience pat{lost, a.base, 0, 0, 0, false};
 
   state_copy(a.st_in, &sh);
   if (threadIdx.x == 0) {
@@ -885,7 +885,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   const int nw = (blockDim.x >> 6) - 1;
   const int tile = blockIdx.x, tiles = gridDim.x;
   const unsigned base = (unsigned)a.base;
-  Patience pat{&a.hs->lost, a.base, 0, 0, 0};
+  Patience pat{&a.hs->lost, a.base, 0, 0, 0, false};
 
   state_copy(a.st_in, &sh);
   if (threadIdx.x == 0) lost = 0;
