@@ -16,6 +16,7 @@ SOURCES = [os.path.join(HERE, "csrc", "plcg_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_team.hip"),
            os.path.join(HERE, "csrc", "plcg_team_var.hip"),
            os.path.join(HERE, "csrc", "plcg_team_batch.hip"),
+           os.path.join(HERE, "csrc", "plcg_team_csr.hip"),
            os.path.join(HERE, "csrc", "plcg_batch_kernels.hip"),
            os.path.join(HERE, "csrc", "plcg_noalloc.hip"),
            os.path.join(HERE, "csrc", "plcg_engine.cpp"),

@@ -442,7 +442,8 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   if (h->method == PLCG_METHOD_CG)
     PLCG_HIP(launch_cg_team(a, h->d3, s));
   else
-    PLCG_HIP(launch_plcg_team(a, h->l, h->d3, s));
+    PLCG_HIP(h->od.ell_k > 0 ? launch_plcg_team_csr(a, h->l, s)
+                             : launch_plcg_team(a, h->l, h->d3, s));
   tl.launched();
   if ((e = tl.end_group()) != PLCG_OK) return e;
   PLCG_HIP(wait_stream(h, s));
@@ -1256,8 +1257,8 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
     else if (cfg->launch_mode == PLCG_LAUNCH_RESIDENT)
       return fail(PLCG_E_INVALID, "PLCG_LAUNCH_RESIDENT: too many stored entries");
   }
-  // Team launches: FP64 solves of the constant and the Jacobi-scaled variable stencils under
-  // AUTO.  A caller who names the
+  // Team launches: FP64 solves of the constant and the Jacobi-scaled variable stencils, and
+  // p(l)-CG of assembled matrices in their ELL form, under AUTO.  A caller who names the
   // launch mode or the x cadence gets the kernels that have them.  Systems that the resident
   // kernels take go to a team where a column of registers per thread beats their strided LDS
   // reads (us per iteration, resident against team, whole solves): 64^2 p(1) 2.87 / 2.07,
@@ -1266,12 +1267,15 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
   // p(2) 2.06 / 2.40 (20 lanes of 64), 12 x 10 x 8 p(2) 2.70 / 3.38, 1 x 4000 p(2) 6.6 / 7.5, and CG over more than one workgroup 2.67 / 3.41
   // at 100 x 37: its two sums wait for other workgroups.
   const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
+  const bool rows = op->kind == PLCG_OP_CSR && pl && h->l <= kTeamLMax && h->od.ell_k > 0 &&
+                    h->res_kind < 0;
   int cus = 0;
   if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO &&
-      h->precision == PLCG_PREC_FP64 && stencil && (!h->var || h->jacobi) && h->device >= 0 &&
-      h->device < kMaxDevices &&
+      h->precision == PLCG_PREC_FP64 && ((stencil && (!h->var || h->jacobi)) || rows) &&
+      h->device >= 0 && h->device < kMaxDevices &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess)
-    h->team = team_plan(pl ? 1 : 0, h->l, h->d3, h->var, h->op.nx, h->op.ny, h->op.nz, cus,
+    h->team = rows ? team_rows_plan((int)n, h->od.ell_k, cus, &h->team_geom) :
+              team_plan(pl ? 1 : 0, h->l, h->d3, h->var, h->op.nx, h->op.ny, h->op.nz, cus,
                         &h->team_geom) &&
               (h->res_kind < 0 ||
                (n >= kTeamMinUnknowns && h->op.nx >= (pl && h->d3 ? 16 : 32) && n / h->op.nx >= 16 &&

@@ -195,4 +195,33 @@ inline bool team_plan(int method_plcg, int l, bool d3, bool var, int nx, int ny,
   return false;
 }
 
+// Assembled matrices (their ELL copy of k entries per row): entries per row that the
+// kernels of two widths take, with as many rows per thread as their registers allow.
+constexpr int kRowsShort = 5, kRowsLong = 9;
+inline int team_rows_v(int k) { return k <= kRowsShort ? 2 : 1; }
+// The cut of n rows: in order, wave by wave, over up to `tiles` workgroups.  Few tiles, as
+// with the stencils, but the gathers of a workgroup share its CU's path to memory: 11
+// streaming waves while there are tiles left, 15 with one row per thread (us per iteration,
+// 11 / 15 waves of two rows, 15 of one: 300 x 201 p(1) 3.04 2.95 2.90, p(2) 2.74 2.98 2.95, p(3) 2.38
+// 3.07 2.73; 400 x 300 p(2) 3.06 3.22 3.38; with 4 waves of one row 4.01 and 4.33;
+// 60 x 50 x 40, seven entries, p(2) 4.36 with 15, 4.96 with 8).
+inline bool team_rows_plan(int n, int k, int tiles, TeamGeom *out) {
+  if (tiles > kTeamTiles) tiles = kTeamTiles;
+  if (n < 1 || k < 1 || k > kRowsLong || tiles < 1) return false;
+  const int v = team_rows_v(k), waves = (n - 1) / (64 * v) + 1;
+  int wz = (waves - 1) / tiles + 1;
+  const int want = v == 2 ? 11 : kTeamWaves;
+  if (wz > kTeamWaves) return false;
+  if (wz < want) wz = want;
+  TeamGeom g{};
+  g.nx = n;
+  g.ny = g.nz = g.gy = g.gz = g.wy = 1;
+  g.gx = (waves - 1) / wz + 1;
+  g.wz = (waves - 1) / g.gx + 1;
+  g.v = v;
+  g.words = 2 * g.wz * 64 * v;       // four copies of the unknowns' words, where faces have two
+  *out = g;
+  return team_mail_bytes(g) <= kTeamMailMax;
+}
+
 }  // namespace plcg

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void slots_team_kernel(TeamS
   const int last = run.i0 + b.sweeps - 1, end = run.m + L;
   a.imax = last < end ? last : end;
   a.hist = nullptr;
-  team_sweeps<L, team_slot_v(L, D3), D3, true>(a, run);
+  team_sweeps<L, GridOp<team_slot_v(L, D3), D3, true>>(a, run);
 }
 
 template <int L, bool D3>

@@ -521,6 +521,50 @@ __device__ inline void halo_add(const Place<V, D3> &pl, const Edges<V, D3, VAR> 
   s[V - 1] = edge_add<VAR>(ed.z(pl, V), h.zhi, s[V - 1]);
 }
 
+// A streaming wave's part of the operator, as team_sweeps uses it: its unknowns, the
+// posting of z_i (tag: of sweep i) and A z_i in two steps, the neighbours' request and
+// their sum.  This one: the stencils.
+template <int V_, bool D3_, bool VAR>
+struct GridOp {
+  static constexpr int V = V_;
+  static constexpr bool D3 = D3_;
+  static constexpr int SR = shared_rows<V, D3>();
+  struct Shared {
+    double rows[2][kTeamWaves][SR][64];            // z_i rows by sweep parity
+    Edges<V, D3, VAR> edges;
+  };
+  using Words = HaloWords;
+  const Place<V, D3> pl;
+  const TeamGeom &g;
+  Shared &sh;
+  const int copy_bytes;
+  const rsrc_t mail;
+  __device__ inline GridOp(const TeamArgs &a, int tile, int tiles, int sw, Shared &s)
+      : pl(a.g, tile, sw), g(a.g), sh(s), copy_bytes(tiles * a.g.words * kWordBytes),
+        mail(mail_rsrc(a.mail, 2 * copy_bytes)) {}
+  __device__ inline bool in(int v) const { return pl.in(v); }
+  __device__ inline int at(int v) const { return pl.p0 + v * pl.stride; }
+  __device__ inline void prepare(const TeamArgs &a) { sh.edges.load(a.od, pl, a.g); }
+  __device__ inline int copy(int i) const { return (i & 1) * copy_bytes; }
+  __device__ inline void post(int i, unsigned tag, const double (&u)[V]) {
+    halo_post<V, D3>(mail, pl, copy(i), tag, u);
+    rows_put<V, D3, SR>(sh.rows[i & 1], pl, u);
+  }
+  __device__ inline void request(int i, Words &w) { halo_request<V, D3>(mail, pl, copy(i), w); }
+  // neighbour sums of z_i, from the wave, the workgroup and the mail; false: lost
+  __device__ inline bool sums(int i, unsigned tag, const double (&u)[V], Words &w, double (&s)[V],
+                              Patience &pat) {
+    Halo hal;
+    rows_sum<V, D3, VAR, SR>(sh.rows[i & 1], pl, g, sh.edges, u, s);
+    bool ok = halo_wait<V, D3>(mail, pl, copy(i), tag, w, hal, pat);
+    halo_add<V, D3, VAR>(pl, sh.edges, hal, s);
+    return halo_y<V, D3>(mail, pl, copy(i), tag, pat, [&](int v, double y) {
+             s[v] = edge_add<VAR>(sh.edges.y(pl, v, pl.ylo ? 0 : 1), y, s[v]);
+           }) && ok;
+  }
+  __device__ inline double apply(double u, double s) const { return from_sum<D3, VAR>(u, s); }
+};
+
 }  // namespace
 
 // One run of Alg. 1, sweeps i = 0 .. imax, with the per-unknown arithmetic of the
@@ -542,21 +586,21 @@ __device__ inline void halo_add(const Place<V, D3> &pl, const Edges<V, D3, VAR> 
 //
 // RUN is WholeRun, or SlotRun for the sweeps of a batched system: those from i0 on to
 // iend, or to the stop if that is known by then, from the slot's vectors and state and back.
-template <int L, int V, bool D3, bool VAR, typename RUN>
+template <int L, typename OP, typename RUN>
 __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   constexpr int ND = L + 1;
   constexpr int R = L - 1 > 2 ? L - 1 : 2;
   constexpr bool SLOT = RUN::kSlot;
   constexpr int LAG = L >= 3 && !SLOT ? 1 : 0;
-  constexpr int SR = shared_rows<V, D3>();
+  constexpr int V = OP::V;
+  constexpr bool D3 = OP::D3;
   // (also a batched system's x at l = 3, for the registers)
   constexpr bool XL = team_x_in_lds(L, V, D3) || (SLOT && L == 3 && !D3);
   constexpr bool PL = team_p_in_lds(L, V, D3);
   constexpr int NT = kTeamWaves * 64;
-  __shared__ double rows[2][kTeamWaves][SR][64];   // z^{(l)}_i rows by sweep parity
   __shared__ double xs[XL ? V : 1][XL ? NT : 1], ps[PL ? V : 1][PL ? NT : 1];
   __shared__ double red[2][kTeamWaves + 1][4];     // wave sums by sweep parity
-  __shared__ Edges<V, D3, VAR> edges;
+  __shared__ typename OP::Shared ops;
   __shared__ DevState sh;
   __shared__ SweepCoef coef[4];                    // of sweep t, at t & 3
   // The first sweep that does not run: set before a barrier that comes before that
@@ -663,9 +707,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     __syncthreads();
     for (int i = i0; !ended(i); ++i) __syncthreads();
   } else {
-    const Place<V, D3> pl(a.g, tile, wave - 1);
-    const int copy_bytes = tiles * a.g.words * kWordBytes;
-    const rsrc_t mail = mail_rsrc(a.mail, 2 * copy_bytes);
+    OP op(a, tile, tiles, wave - 1, ops);
     double zl[R][V], zk[L][2][V], pr[PL ? 1 : V], xr[XL ? 1 : V];
     // p and x are touched once a sweep: the widest kernels keep them in LDS
     const int slot = threadIdx.x - 64;
@@ -683,11 +725,11 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     if constexpr (SLOT) {
 #pragma unroll
       for (int v = 0; v < V; ++v)
-        run.template load<L, R>(pl.in(v), pl.p0 + v * pl.stride, zl, zk, p(v), x(v), v);
+        run.template load<L, R>(op.in(v), op.at(v), zl, zk, p(v), x(v), v);
     } else {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const double z0 = pl.in(v) ? a.z0[pl.p0 + v * pl.stride] : 0.0;
+        const double z0 = op.in(v) ? a.z0[op.at(v)] : 0.0;
 #pragma unroll
         for (int h = 0; h < R; ++h) zl[h][v] = h == 0 ? z0 : 0.0;
 #pragma unroll
@@ -696,34 +738,24 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
           zk[k][1][v] = 0.0;
         }
         p(v) = 0.0;
-        x(v) = pl.in(v) ? a.x[pl.p0 + v * pl.stride] : 0.0;
+        x(v) = op.in(v) ? a.x[op.at(v)] : 0.0;
       }
     }
-    edges.load(a.od, pl, a.g);
-    halo_post<V, D3>(mail, pl, (i0 & 1) * copy_bytes, base + (unsigned)i0, zl[0]);
-    rows_put<V, D3, SR>(rows[i0 & 1], pl, zl[0]);
+    op.prepare(a);
+    op.post(i0, base + (unsigned)i0, zl[0]);
     __syncthreads();
     int i = i0;
     for (; SLOT || i <= a.imax; ++i) {
       const int t = i - L;
-      const int copy = (i & 1) * copy_bytes, copy_next = copy_bytes - copy;
       const unsigned tag = base + (unsigned)i;
       SweepCoef cf;
-      HaloWords hw;
+      typename OP::Words words;
       double s[V];
       if (L >= 2 && ended(i)) break;
       pat.reset(i - i0 <= 1);
-      halo_request<V, D3>(mail, pl, copy, hw);
-      // neighbour sums of z_i, from the wave, the workgroup and the mail
+      op.request(i, words);
       auto neighbours = [&]() {
-        Halo hal;
-        rows_sum<V, D3, VAR, SR>(rows[i & 1], pl, a.g, edges, zl[0], s);
-        bool ok = halo_wait<V, D3>(mail, pl, copy, tag, hw, hal, pat);
-        halo_add<V, D3, VAR>(pl, edges, hal, s);
-        ok = halo_y<V, D3>(mail, pl, copy, tag, pat, [&](int v, double u) {
-               s[v] = edge_add<VAR>(edges.y(pl, v, pl.ylo ? 0 : 1), u, s[v]);
-             }) && ok;
-        if (!ok) lose(L == 1 ? i : i + 1);
+        if (!op.sums(i, tag, zl[0], words, s, pat)) lose(L == 1 ? i : i + 1);
       };
       // bases k = l-1 .. 0, p_t and x_t: nothing here needs A z_i.  (t = 0: the
       // previous vectors are zero, and so are their coefficients.)
@@ -760,21 +792,20 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
           const double zc = zl[0][v];
-          const double w = from_sum<D3, VAR>(zc, s[v]);
+          const double w = op.apply(zc, s[v]);
           const double zn = fma(-cf.dm1, zl[1][v], fma(-cf.gam, zc, w)) * cf.inv_del;
-          s[v] = pl.in(v) ? zn : 0.0;
+          s[v] = op.in(v) ? zn : 0.0;
         }
       } else {
         const double sigma_i = sh.sigma[i];
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          const double w = from_sum<D3, VAR>(zl[0][v], s[v]);
+          const double w = op.apply(zl[0][v], s[v]);
           const double zn = fma(-sigma_i, zl[0][v], w);
-          s[v] = pl.in(v) ? zn : 0.0;
+          s[v] = op.in(v) ? zn : 0.0;
         }
       }
-      halo_post<V, D3>(mail, pl, copy_next, tag + 1, s);
-      rows_put<V, D3, SR>(rows[(i + 1) & 1], pl, s);
+      op.post(i + 1, tag + 1, s);
       if constexpr (L == 1) {
         if (t >= 0) recurrences();
       }
@@ -823,13 +854,13 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
         const bool over = stop_at <= i || i - L > run.m;
 #pragma unroll
         for (int v = 0; v < V; ++v)
-          if (pl.in(v))
-            run.template store<L, R>(i, over, pl.p0 + v * pl.stride, zl, zk, p(v), x(v), v);
+          if (op.in(v))
+            run.template store<L, R>(i, over, op.at(v), zl, zk, p(v), x(v), v);
       }
     } else {
 #pragma unroll
       for (int v = 0; v < V; ++v)
-        if (pl.in(v)) a.x_out[pl.p0 + v * pl.stride] = x(v);
+        if (op.in(v)) a.x_out[op.at(v)] = x(v);
     }
   }
   if constexpr (SLOT) return;
@@ -852,7 +883,7 @@ struct WholeRun {
 
 template <int L, int V, bool D3, bool VAR>
 __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamArgs a) {
-  team_sweeps<L, V, D3, VAR>(a, WholeRun{});
+  team_sweeps<L, GridOp<V, D3, VAR>>(a, WholeRun{});
 }
 
 // Classic CG (Sec. 2.1), iterations k = 0 .. imax - 1 and the stopping test of

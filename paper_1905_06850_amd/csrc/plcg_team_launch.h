@@ -30,6 +30,8 @@ hipError_t launch_cg_team(const TeamArgs &a, bool d3, hipStream_t s);
 // The same for a.od.sx != NULL (plcg_team_var.hip); the launchers above hand over to these.
 hipError_t launch_plcg_team_var(const TeamArgs &a, int l, bool d3, hipStream_t s);
 hipError_t launch_cg_team_var(const TeamArgs &a, bool d3, hipStream_t s);
+// p(l)-CG for a.od.ell_k > 0, g from team_rows_plan (plcg_team_csr.hip).
+hipError_t launch_plcg_team_csr(const TeamArgs &a, int l, hipStream_t s);
 
 // A batched system's tiles in a team launch of several systems.
 struct TeamSlot {
