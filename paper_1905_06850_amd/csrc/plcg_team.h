@@ -16,6 +16,7 @@ namespace plcg {
 
 constexpr int kTeamWaves = 15;        // streaming waves per workgroup, beside one owner wave
 constexpr int kTeamTiles = 256;       // tiles at most (one workgroup per CU)
+constexpr int kTeamXcds = 8;          // XCDs that share the tiles of a launch
 constexpr int kTeamRing = 16;         // slots of the posted products, by column
 constexpr int kTeamProducts = 8;      // words of a workgroup's products of a column: a line
                                       // of 128 bytes of its own, l + 1 <= 4 of them used
@@ -36,6 +37,7 @@ struct TeamGeom {
   int32_t wy, wz, v;
   int32_t rx, ry, rz;                 // words of one x, y and z face of a tile
   int32_t words;                      // words of a tile's mail: two faces of each kind
+  int32_t near;                       // the tiles' workgroups share an XCD
 };
 
 PLCG_HD inline int team_tiles(const TeamGeom &g) { return g.gx * g.gy * g.gz; }
@@ -170,8 +172,16 @@ inline bool team_cut(int nx, int ny, int nz, int v, int tiles, TeamGeom *out) {
 // against 2.28 with two tiles, 60 x 40 p(2) v = 4 1.73 against 1.92, CG v = 5 1.95 against
 // 3.06), with the most unknowns per thread that stay in registers: fewer waves share the
 // SIMDs and the barriers (37 x 53 CG v = 4 / 5 / 6 2.42 2.21 2.32, 64^2 - 2.44 2.28).
-// So: one tile if it fits with v = one (CG also 6); else the smallest v from `lo` up to `hi` with at most `cap` tiles, else hi, else the
-// smallest larger v that fits at all.  false: the system is too large (or too narrow: the
+// Tiles of one XCD (up to 32 of 256) answer each other sooner, 1050 clocks from post to
+// poll against 1570, so such launches put them there (near): 100 x 80 CG 3.98 -> 3.15, p(1)
+// 2.55 -> 2.13, p(2) 2.01 -> 2.00, p(3) 1.91 -> 1.80; 24^3 CG 4.41 -> 4.01, p(1) 2.66 -> 2.52, but p(2)
+// 2.57 -> 2.66.  In 2D where two exchanges follow each other, CG and p(1), it also pays to
+// take more unknowns per thread for it: 300 x 200 CG 4.29 -> 3.83 (v = 2 -> 3), p(1) 2.85 ->
+// 2.62 (3 -> 4), 400 x 300 CG 4.58 -> 4.45 (3 -> 5), but p(1) 2.97 -> 3.07 (4 -> 5); not in 3D,
+// where a tile's faces grow with it: 36^3 CG 4.63 -> 5.43.
+// So: one tile if it fits with v = one (CG also 6); else, in 2D, CG and p(1), the smallest v up
+// to `near` with the tiles of one XCD; else the smallest v from `lo` up to `hi` with at
+// most `cap` tiles, else hi, else the smallest larger v that fits at all.  false: the system is too large (or too narrow: the
 // lanes of a wave lie along x), or its face mail would outgrow kTeamMailMax.
 inline bool team_plan(int method_plcg, int l, bool d3, bool var, int nx, int ny, int nz, int tiles,
                       TeamGeom *out) {
@@ -185,12 +195,20 @@ inline bool team_plan(int method_plcg, int l, bool d3, bool var, int nx, int ny,
     if (team_cut(nx, d3 ? ny : 1, d3 ? nz : ny, v, 1, out) &&
         (v > one || method_plcg || out->wy * out->wz <= 11))
       return true;
+  const int xcd = tiles / kTeamXcds, near = d3 ? 0 : !method_plcg ? 5 : l == 1 ? 4 : 0;
+  for (int v : kTeamWidths)
+    if (v <= near && v <= vmax && team_cut(nx, 1, ny, v, xcd, out)) {
+      out->near = 1;
+      return true;
+    }
   for (int pass = 0; pass < 2; ++pass)
     for (int v : kTeamWidths) {
       if (v > vmax) break;
       if (pass == 0 ? (v < lo || v > hi) : v < hi) continue;
-      if (team_cut(nx, d3 ? ny : 1, d3 ? nz : ny, v, pass == 0 && cap < tiles ? cap : tiles, out))
+      if (team_cut(nx, d3 ? ny : 1, d3 ? nz : ny, v, pass == 0 && cap < tiles ? cap : tiles, out)) {
+        out->near = team_tiles(*out) <= xcd && !(method_plcg && l == 2 && d3);
         return team_mail_bytes(*out) <= kTeamMailMax;
+      }
     }
   return false;
 }
@@ -204,7 +222,8 @@ inline int team_rows_v(int k) { return k <= kRowsShort ? 2 : 1; }
 // streaming waves while there are tiles left, 15 with one row per thread (us per iteration,
 // 11 / 15 waves of two rows, 15 of one: 300 x 201 p(1) 3.04 2.95 2.90, p(2) 2.74 2.98 2.95, p(3) 2.38
 // 3.07 2.73; 400 x 300 p(2) 3.06 3.22 3.38; with 4 waves of one row 4.01 and 4.33;
-// 60 x 50 x 40, seven entries, p(2) 4.36 with 15, 4.96 with 8).
+// 60 x 50 x 40, seven entries, p(2) 4.36 with 15, 4.96 with 8).  On one XCD up to half its
+// CUs' number of tiles: 100 x 77 p(1) 2.63 -> 2.36; with 30 tiles 2.75 -> 2.87.
 inline bool team_rows_plan(int n, int k, int tiles, TeamGeom *out) {
   if (tiles > kTeamTiles) tiles = kTeamTiles;
   if (n < 1 || k < 1 || k > kRowsLong || tiles < 1) return false;
@@ -219,6 +238,7 @@ inline bool team_rows_plan(int n, int k, int tiles, TeamGeom *out) {
   g.gx = (waves - 1) / wz + 1;
   g.wz = (waves - 1) / g.gx + 1;
   g.v = v;
+  g.near = g.gx > 1 && g.gx <= tiles / (2 * kTeamXcds);
   g.words = 2 * g.wz * 64 * v;       // four copies of the unknowns' words, where faces have two
   *out = g;
   return team_mail_bytes(g) <= kTeamMailMax;

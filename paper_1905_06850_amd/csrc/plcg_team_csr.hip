@@ -104,12 +104,13 @@ struct RowsOp {
 
 template <int L, int V, int K>
 __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void rows_team_kernel(TeamArgs a) {
-  team_sweeps<L, RowsOp<V, K>>(a, WholeRun{});
+  if (own_tile(a) < 0) return;
+  team_sweeps<L, RowsOp<V, K>>(a, WholeRun{a});
 }
 
 template <int L>
 static hipError_t launch_rows(const TeamArgs &a, hipStream_t s) {
-  const dim3 grid(team_tiles(a.g)), block(team_threads(a.g));
+  const dim3 grid(team_grid(a)), block(team_threads(a.g));
   if (a.g.v == 2 && a.od.ell_k <= kRowsShort)
     hipLaunchKernelGGL((rows_team_kernel<L, 2, kRowsShort>), grid, block, 0, s, a);
   else if (a.g.v == 1 && a.od.ell_k <= kRowsLong)

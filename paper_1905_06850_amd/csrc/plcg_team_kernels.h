@@ -72,6 +72,13 @@ __device__ inline double word_value(const word4 &w) {
 // Loads after this are new ones, whatever was loaded from there before.
 __device__ inline void fresh() { asm volatile("" ::: "memory"); }
 
+// The workgroup's tile, or -1.  Workgroups are dealt to the XCDs in turn, so that of a near
+// launch, which has kXcds of them per tile, the tiles' ones share the first XCD.
+__device__ inline int own_tile(const TeamArgs &a) {
+  if (a.g.near == 0) return blockIdx.x;
+  return blockIdx.x % kXcds == 0 ? (int)(blockIdx.x / kXcds) : -1;
+}
+
 // The time limit of a wait, and what ends it early: another workgroup's loss.
 struct Patience {
   int32_t *lost;
@@ -611,7 +618,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = SLOT ? a.g.wy * a.g.wz : (blockDim.x >> 6) - 1;
-  const int tile = run.tile(), tiles = SLOT ? team_tiles(a.g) : gridDim.x;
+  const int tile = run.tile(), tiles = team_tiles(a.g);
   const int i0 = run.first();
   const unsigned base = (unsigned)(a.base - i0);   // the tag of sweep i is base + i
   int32_t *const lost = run.lost(a);
@@ -875,7 +882,8 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
 // A whole segment of a solve: the launch's workgroups are the system's tiles.
 struct WholeRun {
   static constexpr bool kSlot = false;
-  __device__ inline int tile() const { return blockIdx.x; }
+  const TeamArgs &a;
+  __device__ inline int tile() const { return own_tile(a); }
   __device__ inline int first() const { return 0; }
   __device__ inline int post_offset() const { return 0; }
   __device__ inline int32_t *lost(const TeamArgs &a) const { return &a.hs->lost; }
@@ -883,7 +891,8 @@ struct WholeRun {
 
 template <int L, int V, bool D3, bool VAR>
 __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamArgs a) {
-  team_sweeps<L, GridOp<V, D3, VAR>>(a, WholeRun{});
+  if (own_tile(a) < 0) return;
+  team_sweeps<L, GridOp<V, D3, VAR>>(a, WholeRun{a});
 }
 
 // Classic CG (Sec. 2.1), iterations k = 0 .. imax - 1 and the stopping test of
@@ -900,6 +909,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void plcg_team_kernel(TeamAr
 // q = A p is then formed a second time for r -= alpha q instead of being held.
 template <int V, bool D3, bool VAR>
 __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs a) {
+  if (own_tile(a) < 0) return;
   constexpr int SR = shared_rows<V, D3>();
   constexpr bool XL = !D3 && V > 6;
   constexpr bool QK = !XL && !(D3 && V > 4);    // q held
@@ -914,7 +924,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = (blockDim.x >> 6) - 1;
-  const int tile = blockIdx.x, tiles = gridDim.x;
+  const int tile = own_tile(a), tiles = team_tiles(a.g);
   const unsigned base = (unsigned)a.base;
   Patience pat{&a.hs->lost, a.base, 0, 0, 0, false};
 
@@ -1133,7 +1143,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
 template <bool VAR, int L, int V, bool D3>
 hipError_t launch_plcg_team_lv(const TeamArgs &a, hipStream_t s) {
   if constexpr (V <= team_vmax(1, L, D3, VAR)) {
-    hipLaunchKernelGGL((plcg_team_kernel<L, V, D3, VAR>), dim3(team_tiles(a.g)),
+    hipLaunchKernelGGL((plcg_team_kernel<L, V, D3, VAR>), dim3(team_grid(a)),
                        dim3(team_threads(a.g)), 0, s, a);
     return hipGetLastError();
   }
@@ -1168,7 +1178,7 @@ hipError_t launch_plcg_team_of(const TeamArgs &a, int l, bool d3, hipStream_t s)
 template <bool VAR, int V, bool D3>
 hipError_t launch_cg_team_v(const TeamArgs &a, hipStream_t s) {
   if constexpr (V <= team_vmax(0, 1, D3, VAR)) {
-    hipLaunchKernelGGL((cg_team_kernel<V, D3, VAR>), dim3(team_tiles(a.g)),
+    hipLaunchKernelGGL((cg_team_kernel<V, D3, VAR>), dim3(team_grid(a)),
                        dim3(team_threads(a.g)), 0, s, a);
     return hipGetLastError();
   }

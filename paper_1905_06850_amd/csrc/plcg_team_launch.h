@@ -25,6 +25,7 @@ struct TeamArgs {
   int32_t base;              // first tag of this run; tags base .. base + imax + 1 (CG: + 2 imax + 2)
   int32_t imax;              // p(l)-CG: last sweep index m + l; CG: maxit
 };
+inline int team_grid(const TeamArgs &a) { return team_tiles(a.g) * (a.g.near ? kXcds : 1); }
 hipError_t launch_plcg_team(const TeamArgs &a, int l, bool d3, hipStream_t s);
 hipError_t launch_cg_team(const TeamArgs &a, bool d3, hipStream_t s);
 // The same for a.od.sx != NULL (plcg_team_var.hip); the launchers above hand over to these.
