@@ -104,10 +104,10 @@ struct TeamPlace {
 // The variable-coefficient stencils' edge weights share the LDS.
 constexpr int team_vmax(int method_plcg, int l, bool d3, bool var) {
   return var           ? (d3 ? (l == 3 ? 2 : 3) : !method_plcg ? 6 : l == 1 ? 4 : 3)
-         : !method_plcg ? (d3 ? 5 : 10)
+         : !method_plcg ? (d3 ? 6 : 10)
          : l == 1     ? (d3 ? 5 : 6)
          : l == 2     ? (d3 ? 4 : 5)
-         : l == 3     ? 3
+         : l == 3     ? 4
                       : 0;
 }
 // Whether a p(l)-CG team kernel keeps x, and p, in LDS.
@@ -117,6 +117,10 @@ constexpr bool team_x_in_lds(int l, int v, bool d3) {
 constexpr bool team_p_in_lds(int l, int v, bool d3) {
   return team_x_in_lds(l, v, d3) && !(d3 && l == 1);
 }
+// Whether it keeps z_{i-1} there too (l = 3: 8 of the 128 registers at v = 4, without which
+// it spilled).  us per iteration, streaming -> team: 1000 x 901 p(3) 16.1 -> 4.1; 3D CG with
+// v = 6, x in LDS, 128 x 101 x 97 18.3 -> 12.6.
+constexpr bool team_z1_in_lds(int l, int v) { return l == 3 && v >= 4; }
 constexpr int kTeamWidths[] = {2, 3, 4, 5, 6, 7, 8, 10};
 
 // Cuts the grid into at most `tiles` tiles with v unknowns per thread: of the

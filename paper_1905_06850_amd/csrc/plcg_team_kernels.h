@@ -604,8 +604,10 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   // (also a batched system's x at l = 3, for the registers)
   constexpr bool XL = team_x_in_lds(L, V, D3) || (SLOT && L == 3 && !D3);
   constexpr bool PL = team_p_in_lds(L, V, D3);
+  constexpr bool Z1 = !SLOT && team_z1_in_lds(L, V);
   constexpr int NT = kTeamWaves * 64;
   __shared__ double xs[XL ? V : 1][XL ? NT : 1], ps[PL ? V : 1][PL ? NT : 1];
+  __shared__ double z1s[Z1 ? V : 1][Z1 ? NT : 1];
   __shared__ double red[2][kTeamWaves + 1][4];     // wave sums by sweep parity
   __shared__ typename OP::Shared ops;
   __shared__ DevState sh;
@@ -715,8 +717,9 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     for (int i = i0; !ended(i); ++i) __syncthreads();
   } else {
     OP op(a, tile, tiles, wave - 1, ops);
-    double zl[R][V], zk[L][2][V], pr[PL ? 1 : V], xr[XL ? 1 : V];
-    // p and x are touched once a sweep: the widest kernels keep them in LDS
+    static_assert(R == 2, "z_i and z_{i-1}");
+    double zl[Z1 ? 1 : R][V], zk[L][2][V], pr[PL ? 1 : V], xr[XL ? 1 : V];
+    // p, x and z_{i-1} are touched at most twice a sweep: the widest kernels keep them in LDS
     const int slot = threadIdx.x - 64;
     auto x = [&](int v) -> double & {
       if constexpr (XL) return xs[v][slot];
@@ -725,6 +728,10 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     auto p = [&](int v) -> double & {
       if constexpr (PL) return ps[v][slot];
       else return pr[v];
+    };
+    auto z1 = [&](int v) -> double & {
+      if constexpr (Z1) return z1s[v][slot];
+      else return zl[R - 1][v];
     };
     double sig[L];
 #pragma unroll
@@ -737,8 +744,8 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const double z0 = op.in(v) ? a.z0[op.at(v)] : 0.0;
-#pragma unroll
-        for (int h = 0; h < R; ++h) zl[h][v] = h == 0 ? z0 : 0.0;
+        zl[0][v] = z0;
+        z1(v) = 0.0;
 #pragma unroll
         for (int k = 0; k < L; ++k) {
           zk[k][0][v] = k == 0 ? z0 : 0.0;
@@ -800,7 +807,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
         for (int v = 0; v < V; ++v) {
           const double zc = zl[0][v];
           const double w = op.apply(zc, s[v]);
-          const double zn = fma(-cf.dm1, zl[1][v], fma(-cf.gam, zc, w)) * cf.inv_del;
+          const double zn = fma(-cf.dm1, z1(v), fma(-cf.gam, zc, w)) * cf.inv_del;
           s[v] = op.in(v) ? zn : 0.0;
         }
       } else {
@@ -826,7 +833,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
           acc[0] = fma(zn, zk[0][0][v], acc[0]);
           acc[L] = fma(zn, zn, acc[L]);
           if constexpr (L >= 2) acc[L - 1] = fma(zn, zl[0][v], acc[L - 1]);
-          if constexpr (L >= 3) acc[L - 2] = fma(zn, zl[1][v], acc[L - 2]);
+          if constexpr (L >= 3) acc[L - 2] = fma(zn, z1(v), acc[L - 2]);
         }
       } else {
         // start-up: z_{i+1} is also the first vector of basis i+1
@@ -836,7 +843,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
 #pragma unroll
           for (int m = 1; m <= L - 2; ++m) {
             const int h = L - 1 - m;
-            if (h <= i) acc[m] = fma(zn, zl[h][v], acc[m]);
+            if (h <= i) acc[m] = fma(zn, h == 0 ? zl[0][v] : z1(v), acc[m]);
           }
           if (i == L - 1) acc[0] = fma(zn, zk[0][0][v], acc[0]);
 #pragma unroll
@@ -848,8 +855,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       }
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-#pragma unroll
-        for (int h = R - 1; h >= 1; --h) zl[h][v] = zl[h - 1][v];
+        z1(v) = zl[0][v];
         zl[0][v] = s[v];
       }
       const double q = products_sum<ND>(acc);
@@ -911,7 +917,7 @@ template <int V, bool D3, bool VAR>
 __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs a) {
   if (own_tile(a) < 0) return;
   constexpr int SR = shared_rows<V, D3>();
-  constexpr bool XL = !D3 && V > 6;
+  constexpr bool XL = D3 ? V > 5 : V > 6;
   constexpr bool QK = !XL && !(D3 && V > 4);    // q held
   __shared__ double rows[kTeamWaves][SR][64];   // 2D: r rows; 3D: p rows
   __shared__ double py[D3 ? kTeamWaves : 1][D3 ? V : 1][64];   // 3D: p beyond the y side
