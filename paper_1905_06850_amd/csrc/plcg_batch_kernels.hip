@@ -8,7 +8,8 @@
 // launches later, the owner never holds up the streaming workgroups; this is
 // why the batched path runs p(l)-CG with l >= 2.  A system's arithmetic does not
 // depend on which other systems share the launch, so its result is bit for bit
-// the same alone and in any mix.
+// the same alone and in any mix.  (The sweeps of FP64 systems with l = 2 or 3 that fit the
+// chip's registers run in team launches between the ticks, plcg_team_batch.hip.)
 //
 // The operator is the Jacobi-scaled variable-coefficient Laplacian
 // A~ = D^{-1/2} A D^{-1/2} (unit diagonal), with (A u)_p = sum_q c_pq (u_p - u_q)
