@@ -477,13 +477,14 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
   int last_i = -1;
   size_t first_launch = tl.launches();
   plcg_status e;
-  // whole: the segment runs in one launch (resident or team)
+  // whole: the segment runs in one launch (resident or team, which run_team waited for)
+  bool team_ran = false;
   bool whole = h->res_kind >= 0 && std::is_same<S, double>::value && m <= kResIterCap;
   if constexpr (std::is_same<S, double>::value) {
     if (h->team && m <= kTeamIterCap) {
       if ((e = run_team(h, ring[0], x, p[1], imax, imax + 2, s, tl, &whole)) != PLCG_OK) return e;
-      if (whole) last_i = 0;
-      else first_launch = tl.launches();
+      team_ran = whole;
+      if (!whole) first_launch = tl.launches();
     } else if (whole) {
       // the whole segment in one resident launch: state copy 1 in, copy 0 out
       ResArgs ra;
@@ -521,6 +522,20 @@ plcg_status run_segment(plcg_handle *h, S *const (*basis)[2], S *const *ring, S 
     if ((e = tl.end_group()) != PLCG_OK) return e;
     if ((e = throttle(h, s, group, &status)) != PLCG_OK) return e;
     if (status != kRunning) break;
+  }
+  if (team_ran) {
+    // from the launch's record: no second wait, for the copy of x, and no copy of the state
+    // (64^2 p(2) 359 -> 335 us a solve, 37 x 53 CG 374 -> 354)
+    out->final_slot = 0;
+    out->status = hstat(h)->status;
+    out->last_t = hstat(h)->last_t;
+    out->t_done = out->status == kRunning ? m : std::min(std::max(out->last_t, 0), m);
+    out->sweeps_run = std::min(imax, (out->status == kRunning ? imax : out->last_t + l)) + 1;
+    out->rec = hstat(h)->zeta;
+    tl.set_units(first_launch, (uint32_t)out->sweeps_run);
+    h->last_hist_count =
+        std::min(h->hist_cap, std::max(hstat(h)->cols - (out->status == kBroken ? 1 : 0), 0));
+    return PLCG_OK;
   }
   PLCG_HIP(wait_stream(h, s));
   out->final_slot = last_i & 1;
@@ -776,10 +791,12 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
   bool stopped = false;
   size_t first_launch = tl.launches();
   bool whole = h->res_kind >= 0 && maxit <= kResIterCap;   // all iterations in one launch
+  bool team_ran = false;                                   // of a team, already waited for
   if (h->team && maxit <= kTeamIterCap) {
     if ((e = run_team(h, h->cg_r, x, h->cg_q, maxit, 2 * maxit + 4, s, tl, &whole)) != PLCG_OK)
       return e;
     if (!whole) first_launch = tl.launches();
+    team_ran = whole;
   } else if (whole) {
     // all iterations in one resident launch: state copy 1 in, copy 0 out
     ResArgs ra;
@@ -827,10 +844,16 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
     PLCG_HIP(launch_cg_sweep_a(a, s));
     *final_slot = 0;
   }
-  PLCG_HIP(wait_stream(h, s));
-  if (stopped) *final_slot = 1;
   DevState ds;
-  PLCG_HIP(hipMemcpy(&ds, h->st[*final_slot], sizeof(ds), hipMemcpyDeviceToHost));
+  if (team_ran) {       // from the launch's record, as in run_segment
+    ds.status = hstat(h)->status;
+    ds.last_t = hstat(h)->last_t;
+  } else {
+    PLCG_HIP(wait_stream(h, s));
+    if (stopped) *final_slot = 1;
+    PLCG_HIP(hipMemcpy(&ds, h->st[*final_slot], sizeof(ds), hipMemcpyDeviceToHost));
+  }
+  const double rnorm = team_ran ? hstat(h)->zeta : std::sqrt(ds.cg_rho);
   status = ds.status;
   const int iters = status == kRunning ? maxit : ds.last_t;
   // Paired updates left x at x_{iters-1} if iters is odd: add alpha_{iters-1}
@@ -844,7 +867,7 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
     tl.keep(first_launch, 2 * (size_t)iters);   // sweeps A and B of iterations 0 .. iters-1
   res->iters = iters;
   res->spmvs = (int32_t)(1 + iters);
-  res->rec_relres = rref > 0 ? std::sqrt(ds.cg_rho) / rref : 0.0;
+  res->rec_relres = rref > 0 ? rnorm / rref : 0.0;
   res->reason = status == kConverged  ? PLCG_REASON_CONVERGED
                 : status == kCgBreak ? PLCG_REASON_BREAKDOWN
                                      : PLCG_REASON_MAXIT;

@@ -880,8 +880,13 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   __syncthreads();
   if (tile == 0) {
     state_copy(&sh, a.st_out);
-    if (threadIdx.x == 0)
-      publish(sh, a.hs, sh.cols >= 1 ? fabs(sh.zeta[(sh.cols - 1) % kTRing]) : sh.beta, sh.cols);
+    // The record holds all that the host asks of the run, with the residual norm of the
+    // iterate that x_out holds (run_segment's t_done): it need not fetch the state.
+    if (threadIdx.x == 0) {
+      const int m = a.imax - L, t = sh.last_t > 0 ? sh.last_t : 0;
+      const int done = sh.status == kRunning || t > m ? m : t;
+      publish(sh, a.hs, done == 0 ? sh.beta : fabs(sh.zeta[done % kTRing]), sh.cols);
+    }
   }
 }
 
