@@ -450,6 +450,9 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   if (hstat(h)->lost == a.base) {
     tl.set_units(tl.launches() - 1, 0);
     h->team = false;
+    // The lost launch may have left a record of its own; throttle() reads the status
+    // before the first streaming sweep has written one.
+    hstat(h)->status = kRunning;
     return PLCG_OK;
   }
   PLCG_HIP(launch_copy(scratch, x, h->n, s));
