@@ -616,7 +616,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   // sweep's look at it, to a later sweep than any that a wave may be about to look
   // for, so all waves (and, from the same products, all workgroups) leave together.
   __shared__ int stop_at;
-  __shared__ int gone;                             // SLOT: this workgroup lost the run
+  __shared__ int gone;                             // this workgroup lost the run
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = SLOT ? a.g.wy * a.g.wz : (blockDim.x >> 6) - 1;
@@ -629,12 +629,16 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   state_copy(a.st_in, &sh);
   if (threadIdx.x == 0) {
     stop_at = kNever;
-    if constexpr (SLOT) gone = 0;
+    gone = 0;
   }
   __syncthreads();
+  // A wave that loses its wait finishes its sweep (the barriers need it) on words that are
+  // not its neighbours', and its products with it.  They are never posted: without them no
+  // sum of that sweep or a later one is complete anywhere, so that no workgroup goes on, or
+  // ends its run as one that was not lost, on what came of them.
   auto lose = [&](int at) {
     atomicMin(&stop_at, at);
-    if constexpr (SLOT) gone = 1;
+    gone = 1;
     __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   // Whether sweep i does not run.  A batched system's launch ends after sweep iend, but
@@ -695,7 +699,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       // only after all the others have read it.
       const bool over = SLOT && ended(i);
       pat.reset(i - i0 <= 1 + LAG);
-      if (i >= (SLOT ? i0 + 1 : 1) && (running || (over && !gone))) {
+      if (i >= (SLOT ? i0 + 1 : 1) && (running || over) && !gone) {
         own_before = own;
         own = own_products<ND>(red[(i - 1) & 1], nw);
         if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
@@ -982,6 +986,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
     const rsrc_t post = mail_rsrc(a.post, (int)team_post_bytes());
     // a reduction: column 2k is (r_k, r_k), 2k+1 is (p_k, A p_k)
     auto reduce = [&](int c) {
+      if (lost) return;                    // as in team_sweeps: no products of a lost run
       const double own = own_products<1>(red, nw);
       if (tiles > 1) post_products<1>(post, own, c, tile, base + (unsigned)c);
       double t[1];

@@ -1,0 +1,82 @@
+"""Team launches that do not get all their workgroups onto the GPU: a wave of other work
+holds a compute unit that a launch of 256 tiles needs, longer than the launch waits.  The
+launch ends by its bounded waits and the other kernels make the run."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch.device("cuda:0")
+
+
+class Holder:
+    """One wave that occupies a compute unit for a time, on a stream of its own."""
+
+    def __init__(self, dev):
+        self.stream = torch.cuda.Stream(dev)
+        self._sleep(1000)
+        cycles = 2_000_000
+        t0 = time.perf_counter()
+        self._sleep(cycles)
+        self.per_second = cycles / (time.perf_counter() - t0)
+
+    def _sleep(self, cycles):
+        with torch.cuda.stream(self.stream):
+            torch.cuda._sleep(int(cycles))
+        self.stream.synchronize()
+
+    def hold(self, seconds):
+        with torch.cuda.stream(self.stream):
+            torch.cuda._sleep(int(seconds * self.per_second))
+        time.sleep(0.05)       # it runs by now
+
+    def wait(self):
+        self.stream.synchronize()
+
+
+@pytest.fixture(scope="module")
+def holder(dev):
+    return Holder(dev)
+
+
+# plans of 256 tiles whose sixteen waves take all registers of a compute unit
+@pytest.mark.parametrize("dims,method,l", [
+    ((1024, 2300), "cg", 1), ((128, 40, 230), "cg", 1), ((128, 40, 230), "plcg", 1),
+    ((1024, 901), "plcg", 2), ((1024, 901), "plcg", 3)])
+@pytest.mark.parametrize("check_every", [0, 1])
+def test_lost_solve_streams(dev, holder, dims, method, l, check_every):
+    """x and the counts are, bit for bit, those of the streaming kernels, which make the run;
+    so are those of the handle's next solve."""
+    from paper_1905_06850_amd import plcg
+    n = int(np.prod(dims))
+    b = torch.from_numpy(synth.uniform(n, 5)).to(dev)
+    kw = dict(method=method, l=l, lmax=8.0 if len(dims) == 2 else 12.0, check_every=check_every)
+    kind = "2d5" if len(dims) == 2 else "3d7"
+    print(f"[gpu] lost team launch {method} l={l} {dims} check_every={check_every}", flush=True)
+    s = plcg.Solver(kind, dims, launch="streaming", **kw)
+    ref = torch.zeros_like(b)
+    rr = s.solve(b, ref, 1e-30, 100)
+    s.close()
+    s = plcg.Solver(kind, dims, **kw)
+    for k in range(2):
+        x = torch.zeros_like(b)
+        torch.cuda.synchronize()
+        if k == 0:
+            holder.hold(0.5)
+        r = s.solve(b, x, 1e-30, 100)
+        holder.wait()
+        assert (r.seconds > 0.2) == (k == 0)      # the first solve's launch waited, and gave up
+        assert r.iters == rr.iters == 100 and r.reason == rr.reason
+        assert r.rec_relres == rr.rec_relres and r.true_relres == rr.true_relres
+        assert torch.equal(x, ref)
+    s.close()
