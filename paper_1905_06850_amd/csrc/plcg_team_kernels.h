@@ -629,16 +629,17 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   state_copy(a.st_in, &sh);
   if (threadIdx.x == 0) {
     stop_at = kNever;
-    gone = 0;
+    if constexpr (L >= 2) gone = 0;
   }
   __syncthreads();
   // A wave that loses its wait finishes its sweep (the barriers need it) on words that are
   // not its neighbours', and its products with it.  They are never posted: without them no
   // sum of that sweep or a later one is complete anywhere, so that no workgroup goes on, or
-  // ends its run as one that was not lost, on what came of them.
+  // ends its run as one that was not lost, on what came of them.  (l = 1: the wave waits, and
+  // all leave, before the sweep's products are formed.)
   auto lose = [&](int at) {
     atomicMin(&stop_at, at);
-    gone = 1;
+    if constexpr (L >= 2) gone = 1;
     __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   // Whether sweep i does not run.  A batched system's launch ends after sweep iend, but
@@ -699,7 +700,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       // only after all the others have read it.
       const bool over = SLOT && ended(i);
       pat.reset(i - i0 <= 1 + LAG);
-      if (i >= (SLOT ? i0 + 1 : 1) && (running || over) && !gone) {
+      if (i >= (SLOT ? i0 + 1 : 1) && (running || over) && (L == 1 || !gone)) {
         own_before = own;
         own = own_products<ND>(red[(i - 1) & 1], nw);
         if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
