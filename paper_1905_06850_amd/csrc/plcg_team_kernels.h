@@ -936,7 +936,11 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   __shared__ Edges<V, D3, VAR> edges;
   __shared__ double total[2];                   // (r, r), (p, A p)
   __shared__ DevState sh;
-  __shared__ int lost;
+  // Whether this workgroup lost a wait, by the product it was on the way to: [0] is written
+  // between the last barrier of an iteration and that before (r, r) is looked at, [1] from
+  // there to the barrier before (p, A p) is, and each is looked at by all waves right after
+  // its barrier, while none may write it.
+  __shared__ int lost[2];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = (blockDim.x >> 6) - 1;
@@ -945,13 +949,13 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   Patience pat{&a.hs->lost, a.base, 0, 0, 0, false};
 
   state_copy(a.st_in, &sh);
-  if (threadIdx.x == 0) lost = 0;
+  if (threadIdx.x == 0) lost[0] = lost[1] = 0;
   __syncthreads();
   double rho = sh.cg_rho, beta = 0.0;
   const double abs_tol = sh.abs_tol;
   int status = sh.status, last_t = sh.last_t, cols = sh.cols;
-  auto lose = [&]() {
-    lost = 1;
+  auto lose = [&](int q) {
+    lost[q] = 1;
     __hip_atomic_store(&a.hs->lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   // After (r_k, r_k) is known: false when iteration k does not run.
@@ -987,14 +991,14 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
     const rsrc_t post = mail_rsrc(a.post, (int)team_post_bytes());
     // a reduction: column 2k is (r_k, r_k), 2k+1 is (p_k, A p_k)
     auto reduce = [&](int c) {
-      if (lost) return;                    // as in team_sweeps: no products of a lost run
+      if (lost[c & 1]) return;             // as in team_sweeps: no products of a lost run
       const double own = own_products<1>(red, nw);
       if (tiles > 1) post_products<1>(post, own, c, tile, base + (unsigned)c);
       double t[1];
       const bool ok = team_sum<1>(post, c, base + (unsigned)c, tiles, own, t, pat, []() {});
       if (lane == 0) {
         total[c & 1] = t[0];
-        if (!ok) lose();
+        if (!ok) lose(c & 1);
       }
     };
     __syncthreads();                       // the streaming waves' r_0 rows
@@ -1002,12 +1006,12 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
       pat.reset(k == 0);
       if (k >= 1) reduce(2 * k);
       __syncthreads();                     // (r, r), and the faces of r_k
-      if (lost || !next(k)) break;
+      if (lost[0] || !next(k)) break;
       if (D3) __syncthreads();             // p rows
       __syncthreads();                     // wave sums of (p, A p)
       reduce(2 * k + 1);
       __syncthreads();                     // (p, A p)
-      if (lost || !curvature_ok(k)) break;
+      if (lost[1] || !curvature_ok(k)) break;
       __syncthreads();                     // wave sums of (r, r), r rows
     }
   } else {
@@ -1068,13 +1072,13 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
       Halo rh;
       pat.reset(k == 0);
       halo_request<V, D3>(mail, pl, copy, hw);
-      if (!halo_wait<V, D3>(mail, pl, copy, tag, hw, rh, pat)) lose();
+      if (!halo_wait<V, D3>(mail, pl, copy, tag, hw, rh, pat)) lose(0);
       if constexpr (!D3) {
         if (pl.wzi > 0) rh.zlo = rows[pl.sw - 1][SR - 1][lane];
         if (pl.wzi < a.g.wz - 1) rh.zhi = rows[pl.sw + 1][0][lane];
       }
       __syncthreads();
-      if (lost || !next(k)) break;
+      if (lost[0] || !next(k)) break;
       // beta = 0 and p = 0 in iteration 0
 #pragma unroll
       for (int v = 0; v < V; ++v) p[v] = fma(beta, p[v], r[v]);
@@ -1087,7 +1091,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
               double &w = py[pl.sw][v][lane];
               w = fma(beta, w, u);
             }))
-          lose();
+          lose(1);
         __syncthreads();
       }
       double acc[1] = {0.0};
@@ -1104,7 +1108,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
       }
       __syncthreads();
       __syncthreads();
-      if (lost || !curvature_ok(k)) break;
+      if (lost[1] || !curvature_ok(k)) break;
       const double alpha = rho / total[1];
 #pragma unroll
       for (int v = 0; v < V; ++v) {

@@ -51,7 +51,7 @@ def holder(dev):
 
 # plans of 256 tiles whose sixteen waves take all registers of a compute unit
 @pytest.mark.parametrize("dims,method,l", [
-    ((1024, 2300), "cg", 1), ((128, 40, 230), "cg", 1), ((128, 40, 230), "plcg", 1),
+    ((1024, 2300), "cg", 1), ((128, 60, 190), "cg", 1), ((128, 40, 230), "plcg", 1),
     ((1024, 901), "plcg", 2), ((1024, 901), "plcg", 3)])
 @pytest.mark.parametrize("check_every", [0, 1])
 def test_lost_solve_streams(dev, holder, dims, method, l, check_every):
