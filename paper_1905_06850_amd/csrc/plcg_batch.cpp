@@ -438,6 +438,7 @@ int32_t launch_rounds(plcg_batch *b, int sweeps, hipStream_t st) {
   const int tags = team_slot_tags(sweeps);
   if (b->team_base > 0x7fffffff - (int64_t)tags * (int64_t)b->rounds.size()) {
     BHIP(hipMemsetAsync(b->d_mail, 0, b->mail_cap, st));
+    BHIP(hipMemsetAsync(b->d_lost, 0, sizeof(int32_t) * b->slots.size(), st));
     b->team_base = 1;
   }
   TeamSlotsArgs a;

@@ -92,11 +92,24 @@ __device__ void owner_step(const BatchArgs &a, int slot, const SlotDesc &S, cons
                            BatchState *out, const double *part_in, BatchState *sh, double *lds,
                            double *red) {
   constexpr int ND = L + 1;
-  const int lost = a.lost[slot];
+  const bool lost = a.lost[slot] > 0;
   bstate_load(in, sh);
   const int phase = sh->phase;
-  // Sweeps that run in team launches: the state goes on as it is.
-  if (lost == 0 && team_sweeps_slot(a, S, *sh)) {
+  // Sweeps that run in team launches: the state goes on as it is, with the products of a
+  // tick's last sweep, which lie where only the next launch looks for them, summed.  A lost
+  // team launch has changed nothing; this system's ticks run its sweeps from now on.
+  if (team_sweeps_slot(a, S, *sh)) {
+    if (sh->i >= 1 && sh->nparts > 0) {
+      sum_partials<ND>(part_in, sh->nparts, kMaxStream, lds, red);
+      if (threadIdx.x == 0) {
+        for (int m = 0; m < ND && m < 4; ++m) sh->raw[m] = red[m];
+        sh->nparts = 0;
+      }
+    }
+    if (lost && threadIdx.x == 0) {
+      a.lost[slot] = 0;
+      sh->solo = 1;
+    }
     bstate_store(sh, out);
     return;
   }
@@ -109,13 +122,7 @@ __device__ void owner_step(const BatchArgs &a, int slot, const SlotDesc &S, cons
   }
   if (threadIdx.x == 0) {
     BatchState &b = *sh;
-    // A lost team launch may have stored some tiles' x_t and not others': the
-    // solve starts again from what x holds, and its ticks run the sweeps.
-    if (lost != 0) {
-      a.lost[slot] = 0;
-      b.solo = 1;
-      b.phase = kResid;
-    } else switch (phase) {
+    switch (phase) {
       case kInit:
         b.phase = kResid;
         break;

@@ -305,7 +305,8 @@ struct BatchArgs {
   int32_t tick, l;
   int32_t mixed;           // FP32-refined batch: vectors stored in FP32
   int32_t hint;            // streaming cache hints of the sweep phase (kHint* bits)
-  int32_t *lost;           // per slot, not 0: a team launch ended without all its workgroups
+  int32_t *lost;           // per slot, what the last team launch came to: > 0: it was lost (it
+                           // did not get all its workgroups) and has changed nothing
   int32_t team;            // 1: team launches run the sweeps of the slots marked for them
 };
 

@@ -640,7 +640,8 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   auto lose = [&](int at) {
     atomicMin(&stop_at, at);
     if constexpr (L >= 2) gone = 1;
-    __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if constexpr (SLOT) run.settle(a.base, a.base);
+    else __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   // Whether sweep i does not run.  A batched system's launch ends after sweep iend, but
   // not between the column that stops the solve and its last sweep.
@@ -661,15 +662,36 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       EngineIn<L> in;
       double raw[ND];
       if constexpr (L >= 3) in = engine_gather<L>(sh, c);
-      if (!team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat, [&]() {
-            if constexpr (L < 3) in = engine_gather<L>(sh, c);
-          })) {
+      bool ok;
+      for (int tries = 0;; ++tries) {
+        ok = team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat,
+                          [&]() {
+                            if constexpr (L < 3) in = engine_gather<L>(sh, c);
+                          });
+        if constexpr (SLOT) {
+          // Everybody's last sweep is made: the run stands, unless a workgroup that did not
+          // see that in time has given it up first.  One that did not, of a run that stands,
+          // looks again: everything it waits for is there.
+          if (over && tiles > 1) {
+            int fate = 0;
+            if (lane == 0) fate = run.settle(a.base, ok ? -a.base : a.base);
+            if (__builtin_amdgcn_readfirstlane(fate) == a.base) ok = false;
+            else if (!ok && tries == 0) {
+              pat.reset(false);
+              pat.gone = false;
+              continue;
+            }
+          }
+        }
+        break;
+      }
+      if (!ok) {
         if (lane == 0) lose(at);
         running = false;
         return;
       }
       if constexpr (SLOT) {
-        if (over) run.template leave<L>(sh, c, raw);
+        if (over && tile == 0) run.template leave<L>(sh, c, raw);
       }
       if (!over) {
         if (lane == 0) {
@@ -695,18 +717,21 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     __syncthreads();
     int i = i0;
     for (; SLOT || i <= a.imax; ++i) {
-      // SLOT, over: everybody posts the products of the last sweep, of which the next
-      // launch makes column i, and tile 0 collects them, so that it rewrites the state
-      // only after all the others have read it.
+      // SLOT, over: everybody posts and collects the products of the last sweep, of which
+      // the next launch makes column i: then all have read the state that tile 0 rewrites,
+      // and the run is settled before anybody stores a vector.
       const bool over = SLOT && ended(i);
       pat.reset(i - i0 <= 1 + LAG);
       if (i >= (SLOT ? i0 + 1 : 1) && (running || over) && (L == 1 || !gone)) {
         own_before = own;
         own = own_products<ND>(red[(i - 1) & 1], nw);
         if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
-        if (i > LAG && (!over || tile == 0)) column(i - LAG, L == 1 ? i : i + 1, over);
+        if (i > LAG) column(i - LAG, L == 1 ? i : i + 1, over);
       }
-      if (SLOT && over) break;
+      if (SLOT && over) {
+        if (tiles > 1) __syncthreads();
+        break;
+      }
       if (L == 1) __syncthreads();
       if (!SLOT && stop_at <= i) break;
       __syncthreads();
@@ -720,6 +745,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     // waves that this system does not need keep the barriers
     __syncthreads();
     for (int i = i0; !ended(i); ++i) __syncthreads();
+    if (tiles > 1) __syncthreads();
   } else {
     OP op(a, tile, tiles, wave - 1, ops);
     static_assert(R == 2, "z_i and z_{i-1}");
@@ -868,6 +894,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       __syncthreads();
     }
     if constexpr (SLOT) {
+      if (tiles > 1) __syncthreads();      // the run is settled
       if (!gone) {
         const bool over = stop_at <= i || i - L > run.m;
 #pragma unroll

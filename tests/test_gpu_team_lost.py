@@ -80,3 +80,64 @@ def test_lost_solve_streams(dev, holder, dims, method, l, check_every):
         assert r.rec_relres == rr.rec_relres and r.true_relres == rr.true_relres
         assert torch.equal(x, ref)
     s.close()
+
+
+class _Batch:
+    """Systems in a batch of their own, stepped until they are done."""
+
+    def __init__(self, dev, dims, l, maxit, tol=1e-30, seed=3):
+        from paper_1905_06850_amd import plcg
+        self.stream = torch.cuda.current_stream(dev).cuda_stream
+        self.batch = plcg.Batch(l=l, max_slots=len(dims), arena_bytes=1 << 30)
+        self.x, self.b, self.tickets = [], [], []
+        for k, d in enumerate(dims):
+            n = int(np.prod(d))
+            cx, cy, cz = synth.edge_coefficients(d, seed + k)
+            self.b.append(torch.from_numpy(synth.uniform(n, seed + 50 + k)).to(dev))
+            self.x.append(torch.zeros_like(self.b[-1]))
+            self.tickets.append(self.batch.add(d, self.b[-1].data_ptr(), self.x[-1].data_ptr(),
+                                               tol, maxit, self.stream, cx, cy, cz))
+        torch.cuda.synchronize()
+
+    def step(self, ticks=16):
+        self.batch.step(ticks, self.stream)
+
+    def finish(self):
+        done, steps = {}, 0
+        while len(done) < len(self.tickets):
+            self.step()
+            torch.cuda.synchronize()
+            steps += 1
+            assert steps < 2000
+            for k, t in enumerate(self.tickets):
+                if k not in done:
+                    r = self.batch.poll(t)
+                    if r is not None:
+                        done[k] = r
+        self.batch.close()
+        return [done[k] for k in range(len(done))], [x.cpu().numpy() for x in self.x], steps
+
+
+# one system of 256 tiles whose waves take all registers, alone and beside a small one
+@pytest.mark.parametrize("dims,l", [([(1024, 720)], 3), ([(64, 80, 140), (30, 20, 10)], 2)])
+@pytest.mark.parametrize("lead", [1, 3])
+def test_lost_batch_goes_on(dev, holder, dims, l, lead):
+    """A launch lost after `lead` steps: no x-update is lost or made twice, x is that of a
+    batch whose launches all ran (to 1e-8, as the ticks' x in test_gpu_team_batch.py)."""
+    print(f"[gpu] lost batch launch {dims} l={l} after {lead} steps", flush=True)
+    ref, xref, _ = _Batch(dev, dims, l, 300).finish()
+    run = _Batch(dev, dims, l, 300)
+    for _ in range(lead):
+        run.step()
+    torch.cuda.synchronize()
+    holder.hold(0.6)
+    t0 = time.perf_counter()
+    run.step()
+    torch.cuda.current_stream(dev).synchronize()
+    assert time.perf_counter() - t0 > 0.2
+    holder.wait()
+    got, x, _ = run.finish()
+    for k in range(len(dims)):
+        assert got[k].iters == ref[k].iters and got[k].restarts == ref[k].restarts
+        assert got[k].reason == ref[k].reason
+        assert np.linalg.norm(x[k] - xref[k]) <= 1e-8 * np.linalg.norm(xref[k])
