@@ -385,7 +385,9 @@ plcg_status plcg_batch_add(plcg_batch *b, const plcg_system_desc *sys, const dou
                            uint64_t *ticket);
 
 /* Enqueue what advances every system by at least `ticks` steps on `stream` (returns
- * without waiting). */
+ * without waiting).  A system that breaks down on the way and starts again, or whose launch
+ * of many iterations could not run (see PLCG_LAUNCH_AUTO), may be left with some of its steps
+ * for the next call. */
 plcg_status plcg_batch_step(plcg_batch *b, int32_t ticks, void *stream);
 
 /* PLCG_NOT_READY until the system of `ticket` is done; then PLCG_OK with the

@@ -88,6 +88,7 @@ struct plcg_batch {
   std::vector<TeamSlot> team_table;
   std::vector<int32_t> team_blocks;
   bool team_only = false;               // every admitted system is marked
+  int setup_left = 0;                   // ticks that the newest of them may need to its sweeps
   int32_t *d_lost = nullptr;
   char *d_team = nullptr;               // table, then block table
   size_t team_cap = 0;
@@ -110,6 +111,9 @@ struct plcg_batch {
 namespace {
 
 int32_t flush_admissions(plcg_batch *b, hipStream_t st);
+
+// Ticks from a system's admission to its first sweep (kInit .. kScale); its report takes fewer.
+constexpr int kTeamSetup = 4;
 
 void free_graph(plcg_batch *b) {
   if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
@@ -525,14 +529,18 @@ int32_t run_plain(plcg_batch *b, int ticks, hipStream_t st, bool team) {
 }
 
 // Team launches go ahead of the ticks, for kTeamTicks ticks at most at a time (other team
-// launches wait meanwhile).  Where all systems are swept there, the ticks only do the
-// setup (four phases) and the report (three) of a solve.  A caller of a few ticks wants to
+// launches wait meanwhile), but after those that bring new systems to their sweeps.  Where all
+// systems are swept there, the ticks only do the setup (four phases) and the report (three) of
+// a solve: four before the launches while a system may be in its setup, and four after them
+// move every system as far as a tick for each of the t asked for did, but for one that breaks
+// down on the way: its new start takes three ticks, and the sweeps that it has then left of
+// its t are made in the next step.  A caller of a few ticks wants to
 // look again soon and gets a sweep for each; a whole group is worth kTeamSweeps for
 // each, as loading and storing the vectors, the ticks and the wait (40 us together) would
 // else take as long as the sweeps.  A burst of 24 systems of 32^2 .. 256^2 unknowns, p(2),
 // served 16 ticks at a time: 22.9 ms by ticks alone, 5.9, 4.3, 3.5, 3.1 ms with 1, 2, 4, 8
 // sweeps per tick; with 4 a group still takes less than its ticks did (215 us, 320).
-constexpr int kTeamSweeps = 4, kTeamTicks = 16, kTeamSetup = 4;
+constexpr int kTeamSweeps = 4, kTeamTicks = 16;
 
 int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
   {
@@ -552,14 +560,18 @@ int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
       (void)hipGetLastError();
       return run_plain(b, ticks, st, false);
     }
-    while (ticks > 0) {
-      const int t = std::min(ticks, kTeamTicks);
-      int32_t e = launch_rounds(b, t < kTeamTicks ? t : kTeamSweeps * t, st);
-      if (e == PLCG_OK) e = run_plain(b, b->team_only ? std::min(t, kTeamSetup) : t, st, true);
-      if (e != PLCG_OK) return e;
+    int lead = std::min(ticks, b->setup_left);
+    int32_t e = run_plain(b, lead, st, true);
+    while (e == PLCG_OK && ticks > 0) {
+      const int t = std::min(ticks, kTeamTicks), report = std::min(t, kTeamSetup);
+      e = launch_rounds(b, t < kTeamTicks ? t : kTeamSweeps * t, st);
+      const int after = b->team_only ? report : std::max(t - lead, report);
+      if (e == PLCG_OK) e = run_plain(b, after, st, true);
+      b->setup_left = std::max(b->setup_left - lead - after, 0);
       ticks -= t;
+      lead = 0;
     }
-    return PLCG_OK;
+    return e;
   }
   return run_plain(b, ticks, st, false);
 }
@@ -752,6 +764,7 @@ int32_t flush_admissions(plcg_batch *b, hipStream_t st) {
                         hipMemcpyHostToDevice, st));
   }
   BHIP(hipStreamSynchronize(st));
+  b->setup_left = kTeamSetup;
   b->pending_desc.clear();
   b->pending_state.clear();
   b->pending_ticket.clear();

@@ -30,6 +30,8 @@ inline std::function<bool(size_t)> refuse;       // allocations that fail
 inline hipStream_t capturing = nullptr;          // the caller's stream in capture
 inline std::vector<Work> captured;
 inline int capture_faults = 0;                   // calls that a capture does not allow
+inline hipStream_t own_capture = nullptr;        // the library's own capture of its ticks
+inline std::vector<Work> *recording = nullptr;
 
 // solves
 inline bool lose_team = false;                   // team launches of solves are lost
@@ -39,11 +41,14 @@ inline int sweeps = 0;                           // streaming sweeps that did wo
 
 // batches
 inline bool lose_slots = false;                  // team launches of batches are lost
+inline int steps[64];                            // steps that each slot has made
 
 inline void enqueue(hipStream_t s, Work w) {
   std::lock_guard<std::recursive_mutex> lk(mu);
   if (capturing != nullptr && s == capturing)
     captured.push_back(std::move(w));
+  else if (own_capture != nullptr && s == own_capture)
+    recording->push_back(std::move(w));
   else
     queue.push_back(std::move(w));
 }
@@ -75,11 +80,21 @@ inline void reset() {
   lost_status = kRunning;
   converge_t = 1 << 30;
   sweeps = 0;
+  memset(steps, 0, sizeof(steps));
 }
 inline int count(const char *what) {
   int n = 0;
   for (const std::string &s : log) n += s == what;
   return n;
+}
+
+// After a batched system's sweep b.i: the next, or, with m x-updates made, the end.
+inline void sweep(BatchState &b, int l) {
+  ++b.i;
+  if (b.i - l > b.m) {
+    b.total = b.m;
+    b.phase = kFinal;
+  }
 }
 
 inline void publish(const DevState &d, HostStatus *hs, double zeta) {
@@ -96,13 +111,7 @@ inline void publish(const DevState &d, HostStatus *hs, double zeta) {
 
 // ---- the HIP runtime ---------------------------------------------------------
 
-struct FakeGraph {
-  std::vector<fake::Work> work;
-};
-namespace fake {
-inline hipStream_t own_capture = nullptr;        // the library's own capture of its ticks
-inline FakeGraph *recording = nullptr;
-}  // namespace fake
+using FakeGraph = std::vector<fake::Work>;
 
 extern "C" {
 
@@ -230,7 +239,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t g, hipGraphNode_t *
   return hipSuccess;
 }
 hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t s) {
-  for (const fake::Work &w : reinterpret_cast<FakeGraph *>(e)->work) fake::enqueue(s, w);
+  for (const fake::Work &w : *reinterpret_cast<FakeGraph *>(e)) fake::enqueue(s, w);
   return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t g) {
@@ -380,9 +389,71 @@ hipError_t launch_plcg_team_csr(const TeamArgs &a, int, hipStream_t s) {
 
 // ---- batches -------------------------------------------------------------------
 
-hipError_t launch_team_slots(const TeamSlotsArgs &, bool, int, int, hipStream_t) {
+// A tick moves each slot by one phase or sweep, but for the sweeps of team launches.
+hipError_t launch_batch_tick(const BatchArgs &a, int blocks, hipStream_t s) {
+  fake::note("tick");
+  fake::enqueue(s, [a, blocks]() {
+    for (int k = 0; k < blocks; ++k) {
+      if (a.sched[k].y >= 0) continue;
+      const int slot = a.sched[k].x, par = a.tick & 1;
+      const SlotDesc &S = a.slots[slot];
+      BatchState &b = a.state[2 * slot + par];
+      b = a.state[2 * slot + (par ^ 1)];
+      if (a.team != 0 && S.team != 0 && b.solo == 0 && b.phase == kSweep) {
+        if (a.lost[slot] > 0) {
+          a.lost[slot] = 0;
+          b.solo = 1;
+        }
+        continue;
+      }
+      if (b.phase != kEmpty && b.phase != kDone) ++fake::steps[slot];
+      switch (b.phase) {
+        case kInit: b.phase = kResid; break;
+        case kResid: b.phase = kStart; break;
+        case kStart:
+          b.m = S.maxit;
+          b.phase = b.m > 0 ? kScale : kFinal;
+          break;
+        case kScale:
+          b.phase = kSweep;
+          b.i = 0;
+          break;
+        case kSweep: fake::sweep(b, a.l); break;
+        case kFinal: b.phase = kFinal2; break;
+        case kFinal2: b.phase = kReport; break;
+        case kReport: {
+          b.phase = kDone;
+          SlotReport &r = a.reports[slot];
+          r.iters = b.total;
+          r.reason = PLCG_REASON_MAXIT;
+          r.ticket = a.tickets[slot];
+          r.phase = kDone;
+          break;
+        }
+        default: break;
+      }
+    }
+  });
   return hipSuccess;
 }
-hipError_t launch_batch_tick(const BatchArgs &, int, hipStream_t) { return hipSuccess; }
+
+hipError_t launch_team_slots(const TeamSlotsArgs &a, bool, int places, int, hipStream_t s) {
+  fake::note("slots");
+  const bool lose = fake::lose_slots;
+  fake::enqueue(s, [a, places, lose]() {
+    for (int k = 0; k < places; ++k) {
+      const TeamSlot &ts = a.table[a.blocks[k]];
+      if (k != ts.first) continue;
+      BatchState &b = a.state[2 * ts.slot + a.par];
+      if (b.phase != kSweep || b.solo != 0) continue;
+      a.lost[ts.slot] = lose ? a.base : -a.base;
+      for (int n = 0; !lose && n < a.sweeps && b.phase == kSweep; ++n) {
+        ++fake::steps[ts.slot];
+        fake::sweep(b, a.l);
+      }
+    }
+  });
+  return hipSuccess;
+}
 
 }  // namespace plcg

@@ -66,11 +66,80 @@ void lost_record() {
     }
 }
 
+plcg_batch *make_batch(int l, int slots, int use_graph) {
+  plcg_batch_config cfg{};
+  cfg.l = l;
+  cfg.max_slots = slots;
+  cfg.arena_bytes = 64 << 20;
+  cfg.max_restarts = -1;
+  cfg.use_graph = use_graph;
+  plcg_batch *b = nullptr;
+  EXPECT(plcg_batch_create(&cfg, &b) == PLCG_OK, "%s", plcg_last_error());
+  return b;
+}
+
+uint64_t add(plcg_batch *b, int nx, int ny, double *v, int maxit, hipStream_t s = nullptr) {
+  plcg_system_desc d{};
+  d.kind = PLCG_OP_STENCIL2D5;
+  d.nx = nx;
+  d.ny = ny;
+  d.nz = 1;
+  uint64_t t = 0;
+  const plcg_status e = plcg_batch_add(b, &d, v, v, 1e-8, maxit, s, &t);
+  EXPECT(e == PLCG_OK, "plcg_batch_add: %s", plcg_last_error());
+  return t;
+}
+
+// Every step moves every system by as many steps as it is asked for, or to its end: systems
+// that came with this step or an earlier one, that team launches sweep or ticks (lanes mostly
+// idle: the narrow ones), alone or together.
+void step_counts() {
+  double *v = vec(40000);
+  for (int seed = 0; seed < 300 && good; ++seed) {
+    fake::reset();
+    srand(seed);
+    plcg_batch *b = make_batch(2 + seed % 2, 8, seed / 2 % 2);
+    const bool narrow = seed / 4 % 2 != 0;
+    uint64_t ticket[8] = {0};          // by slot: a system gets the first free one
+    bool open[8] = {false};
+    int room = 8;
+    for (int call = 0; call < 12 && good; ++call) {
+      for (int want = rand() % 4; want > 0 && room > 0; --want, --room)
+        for (int k = 0; k < 8; ++k) {
+          if (open[k]) continue;
+          const bool thin = narrow && rand() % 2 == 0;
+          ticket[k] = add(b, thin ? 1 : 20 + rand() % 150, thin ? 3000 : 20 + rand() % 150, v,
+                          rand() % 60);
+          open[k] = true;
+          break;
+        }
+      const int sizes[] = {1, 2, 3, 4, 5, 8, 15, 16, 17, 31, 40};
+      const int ticks = sizes[rand() % 11];
+      memset(fake::steps, 0, sizeof(fake::steps));
+      EXPECT(plcg_batch_step(b, ticks, nullptr) == PLCG_OK, "%s", plcg_last_error());
+      (void)hipStreamSynchronize(nullptr);
+      for (int k = 0; k < 8; ++k) {
+        if (!open[k]) continue;
+        plcg_result r{};
+        const bool done = plcg_batch_poll(b, ticket[k], &r) == PLCG_OK;
+        EXPECT(done || fake::steps[k] >= ticks, "seed %d call %d: system %d made %d of %d steps",
+               seed, call, k, fake::steps[k], ticks);
+        if (done) {
+          open[k] = false;
+          ++room;
+        }
+      }
+    }
+    plcg_batch_destroy(b);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "lost_record") lost_record();
+  else if (name == "step_counts") step_counts();
   else {
     printf("unknown scenario %s\n", name.c_str());
     return 2;
