@@ -542,6 +542,14 @@ int32_t run_plain(plcg_batch *b, int ticks, hipStream_t st, bool team) {
 // sweeps per tick; with 4 a group still takes less than its ticks did (215 us, 320).
 constexpr int kTeamSweeps = 4, kTeamTicks = 16;
 
+// Whether the ticks run the sweeps of a marked system, whose team launch was lost.
+bool any_solo(const plcg_batch *b) {
+  for (size_t s = 0; s < b->slots.size(); ++s)
+    if (b->in_use[s] && static_cast<volatile const SlotReport &>(b->reports[s]).solo != 0)
+      return true;
+  return false;
+}
+
 int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
   {
     int32_t e = flush_admissions(b, st);
@@ -560,12 +568,13 @@ int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
       (void)hipGetLastError();
       return run_plain(b, ticks, st, false);
     }
+    const bool lean = b->team_only && !any_solo(b);
     int lead = std::min(ticks, b->setup_left);
     int32_t e = run_plain(b, lead, st, true);
     while (e == PLCG_OK && ticks > 0) {
       const int t = std::min(ticks, kTeamTicks), report = std::min(t, kTeamSetup);
       e = launch_rounds(b, t < kTeamTicks ? t : kTeamSweeps * t, st);
-      const int after = b->team_only ? report : std::max(t - lead, report);
+      const int after = lean ? report : std::max(t - lead, report);
       if (e == PLCG_OK) e = run_plain(b, after, st, true);
       b->setup_left = std::max(b->setup_left - lead - after, 0);
       ticks -= t;
@@ -742,6 +751,7 @@ int32_t admit(plcg_batch *b, const plcg_system_desc *sys, const Layout &L, bool 
   b->pending_ticket.push_back(tk);
   b->reports[slot].phase = kInit;
   b->reports[slot].ticket = tk;
+  b->reports[slot].solo = 0;
   b->in_use[slot] = 1;
   b->tickets[slot] = tk;
   b->slot_mem[slot] = Block{off, bytes};

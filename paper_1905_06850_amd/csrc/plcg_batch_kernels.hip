@@ -109,6 +109,7 @@ __device__ void owner_step(const BatchArgs &a, int slot, const SlotDesc &S, cons
     if (lost && threadIdx.x == 0) {
       a.lost[slot] = 0;
       sh->solo = 1;
+      a.reports[slot].solo = 1;
     }
     bstate_store(sh, out);
     return;

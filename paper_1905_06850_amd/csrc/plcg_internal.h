@@ -292,7 +292,8 @@ struct SlotReport {
   int32_t phase, reason, iters, restarts;
   double res_scaled, res_orig, rnorm0;
   uint64_t ticket;
-  int32_t outer, pad;
+  int32_t outer;
+  int32_t solo;            // BatchState::solo of the slot's system
 };
 
 struct BatchArgs {

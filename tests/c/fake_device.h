@@ -403,6 +403,7 @@ hipError_t launch_batch_tick(const BatchArgs &a, int blocks, hipStream_t s) {
         if (a.lost[slot] > 0) {
           a.lost[slot] = 0;
           b.solo = 1;
+          a.reports[slot].solo = 1;
         }
         continue;
       }

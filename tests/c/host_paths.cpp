@@ -92,8 +92,9 @@ uint64_t add(plcg_batch *b, int nx, int ny, double *v, int maxit, hipStream_t s 
 
 // Every step moves every system by as many steps as it is asked for, or to its end: systems
 // that came with this step or an earlier one, that team launches sweep or ticks (lanes mostly
-// idle: the narrow ones), alone or together.
-void step_counts() {
+// idle: the narrow ones), alone or together.  lose: now and then all launches of a step are
+// lost, and the systems that they were to sweep are swept by ticks from the next step on.
+void step_counts(bool lose) {
   double *v = vec(40000);
   for (int seed = 0; seed < 300 && good; ++seed) {
     fake::reset();
@@ -116,13 +117,14 @@ void step_counts() {
       const int sizes[] = {1, 2, 3, 4, 5, 8, 15, 16, 17, 31, 40};
       const int ticks = sizes[rand() % 11];
       memset(fake::steps, 0, sizeof(fake::steps));
+      fake::lose_slots = lose && rand() % 3 == 0;
       EXPECT(plcg_batch_step(b, ticks, nullptr) == PLCG_OK, "%s", plcg_last_error());
       (void)hipStreamSynchronize(nullptr);
       for (int k = 0; k < 8; ++k) {
         if (!open[k]) continue;
         plcg_result r{};
         const bool done = plcg_batch_poll(b, ticket[k], &r) == PLCG_OK;
-        EXPECT(done || fake::steps[k] >= ticks, "seed %d call %d: system %d made %d of %d steps",
+        EXPECT(done || fake::lose_slots || fake::steps[k] >= ticks, "seed %d call %d: system %d made %d of %d steps",
                seed, call, k, fake::steps[k], ticks);
         if (done) {
           open[k] = false;
@@ -139,7 +141,8 @@ void step_counts() {
 int main(int argc, char **argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "lost_record") lost_record();
-  else if (name == "step_counts") step_counts();
+  else if (name == "step_counts") step_counts(false);
+  else if (name == "step_counts_lost") step_counts(true);
   else {
     printf("unknown scenario %s\n", name.c_str());
     return 2;

@@ -136,7 +136,9 @@ def test_lost_batch_goes_on(dev, holder, dims, l, lead):
     torch.cuda.current_stream(dev).synchronize()
     assert time.perf_counter() - t0 > 0.2
     holder.wait()
-    got, x, _ = run.finish()
+    got, x, steps = run.finish()
+    # 16 x-updates a step are left to the ticks, beside setup, fill and report
+    assert steps <= (300 + 10 + l) // 16 + 2
     for k in range(len(dims)):
         assert got[k].iters == ref[k].iters and got[k].restarts == ref[k].restarts
         assert got[k].reason == ref[k].reason
