@@ -170,12 +170,21 @@ __device__ inline double products_sum(const double (&a)[ND]) {
 
 // ---- sums across the workgroups --------------------------------------------
 
-// The workgroup's products from the streaming waves' sums: product m in every lane
-// of row m of the owner wave.
+// The workgroup's products from the streaming waves' sums (zeros where there is no wave):
+// product m in every lane of row m of the owner wave.
 template <int ND>
-__device__ inline double own_products(const double (*red)[4], int nw) {
+__device__ inline double own_products(const double (*red)[4]) {
   const int lane = threadIdx.x & 63, k = lane & 15, row = lane >> 4;
-  return row_sum(k < nw && row < ND ? red[k][row] : 0.0);
+  return row_sum(row < ND ? red[k][row] : 0.0);
+}
+// The entry beyond the last wave's makes them NaN.  A wave that loses its wait finishes its
+// sweep, as the barriers need it, on words that were not the awaited ones; its workgroup's
+// products are NaN then, and so is everybody's sum of them: nobody goes on, or ends its run as
+// one that was not lost, on what came of those words.  (As a flag that the owner looks at before it
+// posts them this cost 1 to 3 % of a p(2) sweep, as a NaN in the wave's own sums 1 %.)
+__device__ inline void spoil_products(double (*red)[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) red[kTeamWaves][m] = __builtin_nan("");
 }
 
 // The owner wave posts its workgroup's products of column c.
@@ -616,7 +625,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   // sweep's look at it, to a later sweep than any that a wave may be about to look
   // for, so all waves (and, from the same products, all workgroups) leave together.
   __shared__ int stop_at;
-  __shared__ int gone;                             // this workgroup lost the run
+  __shared__ int gone;                             // SLOT: this workgroup lost the run
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = SLOT ? a.g.wy * a.g.wz : (blockDim.x >> 6) - 1;
@@ -627,19 +636,19 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   Patience pat{lost, a.base, 0, 0, 0, false};
 
   state_copy(a.st_in, &sh);
+  if (threadIdx.x < 2 * (kTeamWaves + 1) * 4) (&red[0][0][0])[threadIdx.x] = 0.0;
   if (threadIdx.x == 0) {
     stop_at = kNever;
-    if constexpr (L >= 2) gone = 0;
+    if constexpr (SLOT) gone = 0;
   }
   __syncthreads();
-  // A wave that loses its wait finishes its sweep (the barriers need it) on words that are
-  // not its neighbours', and its products with it.  They are never posted: without them no
-  // sum of that sweep or a later one is complete anywhere, so that no workgroup goes on, or
-  // ends its run as one that was not lost, on what came of them.  (l = 1: the wave waits, and
-  // all leave, before the sweep's products are formed.)
   auto lose = [&](int at) {
     atomicMin(&stop_at, at);
-    if constexpr (L >= 2) gone = 1;
+    if constexpr (L >= 2) {                  // l = 1: all leave before the sweep's products
+      spoil_products(red[0]);
+      spoil_products(red[1]);
+    }
+    if constexpr (SLOT) gone = 1;
     if constexpr (SLOT) run.settle(a.base, a.base);
     else __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
@@ -662,30 +671,31 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       EngineIn<L> in;
       double raw[ND];
       if constexpr (L >= 3) in = engine_gather<L>(sh, c);
-      bool ok;
-      for (int tries = 0;; ++tries) {
-        ok = team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat,
-                          [&]() {
-                            if constexpr (L < 3) in = engine_gather<L>(sh, c);
-                          });
-        if constexpr (SLOT) {
-          // Everybody's last sweep is made: the run stands, unless a workgroup that did not
-          // see that in time has given it up first.  One that did not, of a run that stands,
-          // looks again: everything it waits for is there.
-          if (over && tiles > 1) {
-            int fate = 0;
-            if (lane == 0) fate = run.settle(a.base, ok ? -a.base : a.base);
-            if (__builtin_amdgcn_readfirstlane(fate) == a.base) ok = false;
-            else if (!ok && tries == 0) {
-              pat.reset(false);
-              pat.gone = false;
-              continue;
-            }
-          }
+      auto sum = [&]() {
+        return team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat,
+                            [&]() {
+                              if constexpr (L < 3) in = engine_gather<L>(sh, c);
+                            });
+      };
+      // SLOT, over: everybody's last sweep is made, and the run stands, unless a workgroup that
+      // did not see that in time has given it up first.  One that did not, of a run that
+      // stands, looks again: everything it waits for is there.
+      auto settled_sum = [&](const auto &run) {
+        for (int tries = 0;; ++tries) {
+          const bool ok = sum();
+          if (!over || tiles == 1) return ok;
+          int fate = 0;
+          if (lane == 0) fate = run.settle(a.base, ok ? -a.base : a.base);
+          if (__builtin_amdgcn_readfirstlane(fate) == a.base) return false;
+          if (ok || tries == 1) return ok;
+          pat.reset(false);
+          pat.gone = false;
         }
-        break;
-      }
-      if (!ok) {
+      };
+      bool lost_sum;
+      if constexpr (SLOT) lost_sum = !settled_sum(run);
+      else lost_sum = !sum();
+      if (lost_sum) {
         if (lane == 0) lose(at);
         running = false;
         return;
@@ -722,9 +732,9 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       // and the run is settled before anybody stores a vector.
       const bool over = SLOT && ended(i);
       pat.reset(i - i0 <= 1 + LAG);
-      if (i >= (SLOT ? i0 + 1 : 1) && (running || over) && (L == 1 || !gone)) {
+      if (i >= (SLOT ? i0 + 1 : 1) && (running || (over && !gone))) {
         own_before = own;
-        own = own_products<ND>(red[(i - 1) & 1], nw);
+        own = own_products<ND>(red[(i - 1) & 1]);
         if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
         if (i > LAG) column(i - LAG, L == 1 ? i : i + 1, over);
       }
@@ -970,12 +980,12 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   __shared__ int lost[2];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = (blockDim.x >> 6) - 1;
   const int tile = own_tile(a), tiles = team_tiles(a.g);
   const unsigned base = (unsigned)a.base;
   Patience pat{&a.hs->lost, a.base, 0, 0, 0, false};
 
   state_copy(a.st_in, &sh);
+  if (threadIdx.x < (kTeamWaves + 1) * 4) (&red[0][0])[threadIdx.x] = 0.0;
   if (threadIdx.x == 0) lost[0] = lost[1] = 0;
   __syncthreads();
   double rho = sh.cg_rho, beta = 0.0;
@@ -983,6 +993,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
   int status = sh.status, last_t = sh.last_t, cols = sh.cols;
   auto lose = [&](int q) {
     lost[q] = 1;
+    spoil_products(red);
     __hip_atomic_store(&a.hs->lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   // After (r_k, r_k) is known: false when iteration k does not run.
@@ -1018,8 +1029,7 @@ __global__ __launch_bounds__(64 * (kTeamWaves + 1)) void cg_team_kernel(TeamArgs
     const rsrc_t post = mail_rsrc(a.post, (int)team_post_bytes());
     // a reduction: column 2k is (r_k, r_k), 2k+1 is (p_k, A p_k)
     auto reduce = [&](int c) {
-      if (lost[c & 1]) return;             // as in team_sweeps: no products of a lost run
-      const double own = own_products<1>(red, nw);
+      const double own = own_products<1>(red);
       if (tiles > 1) post_products<1>(post, own, c, tile, base + (unsigned)c);
       double t[1];
       const bool ok = team_sum<1>(post, c, base + (unsigned)c, tiles, own, t, pat, []() {});
