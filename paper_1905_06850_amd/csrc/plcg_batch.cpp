@@ -457,19 +457,19 @@ int32_t launch_rounds(plcg_batch *b, int sweeps, hipStream_t st) {
   a.sweeps = sweeps;
   a.l = b->l;
   const int32_t *blocks = reinterpret_cast<const int32_t *>(b->d_team + b->team_table.size() * sizeof(TeamSlot));
+  int places = 0;
+  int32_t near = 0;
+  for (const plcg_batch::Round &r : b->rounds) places = std::max(places, r.places);
   TeamTurn &turn = team_turn(b->device);
   std::lock_guard<std::mutex> lk(turn.mu);
-  if (turn.last != nullptr)
-    BHIP(hipStreamWaitEvent(st, turn.last, 0));
-  else
-    BHIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
+  BHIP(turn.enter(b, places, b->cus, st, &near));
   for (const plcg_batch::Round &r : b->rounds) {
     a.blocks = blocks + r.first;
     a.base = b->team_base;      // the rounds share the mail: no tag twice
     b->team_base += tags;
     BHIP(launch_team_slots(a, r.d3, r.places, r.threads, st));
   }
-  BHIP(hipEventRecord(turn.last, st));
+  BHIP(turn.leave(b, false));
   return PLCG_OK;
 }
 
@@ -1004,6 +1004,10 @@ plcg_status plcg_batch_destroy(plcg_batch *b) {
   if (b == nullptr) return PLCG_OK;
   (void)hipSetDevice(b->device);
   (void)hipDeviceSynchronize();
+  if (b->device < kMaxDevices) {
+    std::lock_guard<std::mutex> lk(team_turn(b->device).mu);
+    team_turn(b->device).done(b);
+  }
   free_graph(b);
   for (auto &op : b->ops) (void)hipFree(op.mem);
   if (b->arena) (void)hipFree(b->arena);

@@ -37,6 +37,72 @@ TeamTurn &team_turn(int device) {
   return turns[device];
 }
 
+hipError_t TeamTurn::after(Run &r) {
+  if (r.recorded) return hipSuccess;
+  hipError_t e = hipSuccess;
+  if (r.ev == nullptr) e = hipEventCreateWithFlags(&r.ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(r.ev, r.stream);
+  r.recorded = e == hipSuccess;
+  return e;
+}
+
+hipError_t TeamTurn::enter(const void *owner, int tiles, int cus, hipStream_t s, int32_t *near) {
+  // runs that have ended (those of an owner that waits for them leave by done())
+  for (size_t k = 0; k < runs_.size();) {
+    if (runs_[k].owner != owner && runs_[k].recorded && hipEventQuery(runs_[k].ev) == hipSuccess) {
+      (void)hipEventDestroy(runs_[k].ev);
+      runs_.erase(runs_.begin() + k);
+    } else {
+      ++k;
+    }
+  }
+  Run mine{owner, 0, s, nullptr, false};
+  hipError_t e = hipSuccess;
+  for (size_t k = 0; k < runs_.size(); ++k)
+    if (runs_[k].owner == owner) {
+      // launched earlier, on this stream or another: in order, as one
+      if ((e = after(runs_[k])) != hipSuccess) return e;
+      if ((e = hipStreamWaitEvent(s, runs_[k].ev, 0)) != hipSuccess) return e;
+      mine = runs_[k];
+      runs_.erase(runs_.begin() + k);
+      break;
+    }
+  std::vector<int> needs;
+  int all = 0;
+  for (const Run &r : runs_) {
+    needs.push_back(r.need);
+    all += r.need;
+  }
+  const int per_xcd = cus / kXcds;
+  if (*near != 0 && all + team_need(tiles, true) > per_xcd) *near = 0;
+  const int need = team_need(tiles, *near != 0);
+  const int first = tiles == 1 ? 0 : team_beside(needs.data(), (int)needs.size(), need, per_xcd);
+  for (int k = 0; k < first; ++k) {
+    if ((e = after(runs_[k])) != hipSuccess) return e;
+    if ((e = hipStreamWaitEvent(s, runs_[k].ev, 0)) != hipSuccess) return e;
+  }
+  mine.need = std::max(mine.need, need);
+  mine.stream = s;
+  mine.recorded = false;
+  runs_.push_back(mine);
+  return hipSuccess;
+}
+
+hipError_t TeamTurn::leave(const void *owner, bool waits) {
+  if (runs_.empty() || runs_.back().owner != owner) return hipSuccess;
+  // (a thread's own default stream is another one in the thread that would record the event)
+  return waits && runs_.back().stream != hipStreamPerThread ? hipSuccess : after(runs_.back());
+}
+
+void TeamTurn::done(const void *owner) {
+  for (size_t k = 0; k < runs_.size(); ++k)
+    if (runs_[k].owner == owner) {
+      if (runs_[k].ev != nullptr) (void)hipEventDestroy(runs_[k].ev);
+      runs_.erase(runs_.begin() + k);
+      return;
+    }
+}
+
 }  // namespace plcg
 
 namespace {
@@ -158,6 +224,7 @@ struct plcg_handle {
   bool d3 = false;
   int res_kind = -1;              // operator kind of the resident kernels; -1: streaming
   bool team = false;              // segments run as team launches
+  int cus = 0;                    // of the device
   TeamGeom team_geom{};
   void *team_mail = nullptr, *team_post = nullptr;
   int team_base = 1;              // first tag of the next team launch
@@ -436,17 +503,31 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   h->team_base += tags;
   plcg_status e;
   TeamTurn &turn = team_turn(h->device);
-  std::lock_guard<std::mutex> lk(turn.mu);
-  if (turn.last != nullptr) PLCG_HIP(hipStreamWaitEvent(s, turn.last, 0));
-  if ((e = tl.begin_group()) != PLCG_OK) return e;
-  if (h->method == PLCG_METHOD_CG)
-    PLCG_HIP(launch_cg_team(a, h->d3, s));
-  else
-    PLCG_HIP(h->od.ell_k > 0 ? launch_plcg_team_csr(a, h->l, s)
-                             : launch_plcg_team(a, h->l, h->d3, s));
-  tl.launched();
-  if ((e = tl.end_group()) != PLCG_OK) return e;
-  PLCG_HIP(wait_stream(h, s));
+  struct Done {
+    TeamTurn &turn;
+    const void *owner;
+    ~Done() {
+      std::lock_guard<std::mutex> lk(turn.mu);
+      turn.done(owner);
+    }
+  };
+  {
+    Done done{turn, h};
+    {
+      std::lock_guard<std::mutex> lk(turn.mu);
+      PLCG_HIP(turn.enter(h, team_tiles(a.g), h->cus, s, &a.g.near));
+      if ((e = tl.begin_group()) != PLCG_OK) return e;
+      if (h->method == PLCG_METHOD_CG)
+        PLCG_HIP(launch_cg_team(a, h->d3, s));
+      else
+        PLCG_HIP(h->od.ell_k > 0 ? launch_plcg_team_csr(a, h->l, s)
+                                 : launch_plcg_team(a, h->l, h->d3, s));
+      PLCG_HIP(turn.leave(h, true));
+    }
+    tl.launched();
+    if ((e = tl.end_group()) != PLCG_OK) return e;
+    PLCG_HIP(wait_stream(h, s));
+  }
   if (hstat(h)->lost == a.base) {
     tl.set_units(tl.launches() - 1, 0);
     h->team = false;
@@ -1295,7 +1376,7 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
   const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
   const bool rows = op->kind == PLCG_OP_CSR && pl && h->l <= kTeamLMax && h->od.ell_k > 0 &&
                     h->res_kind < 0;
-  int cus = 0;
+  int &cus = h->cus;
   if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO &&
       h->precision == PLCG_PREC_FP64 && ((stencil && (!h->var || h->jacobi)) || rows) &&
       h->device >= 0 && h->device < kMaxDevices &&

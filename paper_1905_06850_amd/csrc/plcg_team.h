@@ -50,6 +50,23 @@ constexpr size_t team_post_bytes() {
   return (size_t)kTeamRing * kTeamTiles * kTeamProducts * kWordBytes;
 }
 
+// CUs of one XCD that a launch may need: its tiles, if they share one, else an equal part of
+// them on every XCD.
+inline int team_need(int tiles, bool near) {
+  return near ? tiles : (tiles + kTeamXcds - 1) / kTeamXcds;
+}
+// Of the n launches that may be on the GPU or waiting for it (what each needs, oldest
+// first), the first that a new one of `need` can be beside, all later ones too: what they need
+// together, on the XCD that they may share, is there.  The new one has to wait for those
+// before it.  So of any launches that run at once the newest has counted all the others, and
+// none of them waits for a CU that another holds while it waits itself.  (Which XCD
+// a launch's first workgroup goes to differs by hardware queue and is not known here.)
+inline int team_beside(const int *needs, int n, int need, int per_xcd) {
+  int first = n, sum = need;
+  while (first > 0 && sum + needs[first - 1] <= per_xcd) sum += needs[--first];
+  return first;
+}
+
 // A streaming wave's place in the grid and its share of the mail, uniform in the wave:
 // byte offsets within one parity copy, to which a lane adds 16 times its number (z and
 // y faces; row v of a y face 64 v words on) or 16 times the row it stands for (x faces:

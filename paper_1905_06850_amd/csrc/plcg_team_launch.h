@@ -3,6 +3,7 @@
 #pragma once
 
 #include <mutex>
+#include <vector>
 
 #include "plcg_internal.h"
 #include "plcg_team.h"
@@ -61,14 +62,37 @@ constexpr int team_slot_tags(int sweeps) { return sweeps + 2 * kTeamLMax + 2; }
 hipError_t launch_team_slots(const TeamSlotsArgs &a, bool d3, int places, int threads,
                              hipStream_t s);
 
-// A team launch needs all its workgroups on the GPU at once, so two of them at a time would
-// wait for each other: one runs on a device at a time (within the process; across
-// processes the kernels' bounded waits and the streaming sweeps take over).  Solves, which
-// wait for their launch, hold `mu` meanwhile; launches that are only enqueued hold it while
-// they are, wait for `last` and record it.
-struct TeamTurn {
-  std::mutex mu;
-  hipEvent_t last = nullptr;
+// A team launch needs all its workgroups on the GPU at once, so two that do not fit
+// there together would wait for each other: they take turns (within the process; across
+// processes the kernels' bounded waits and the streaming sweeps take over).  A launch is made
+// under the lock, between enter() and leave(), and is waited for by later ones on the GPU;
+// the host waits for nothing but the lock.
+static_assert(kTeamXcds == kXcds, "the plans' XCDs are the device's");
+class TeamTurn {
+ public:
+  // Makes the stream wait until a launch of `tiles` workgroups can run; owner: what makes it
+  // (a solve's or a batch's handle, which has one entry).  *near as planned on entry: a launch
+  // that would have to wait for a place on one XCD spreads over all of them (the same tiles and
+  // the same bits; 100 x 80 CG 3.98 us per iteration instead of 3.15).  A launch of one
+  // workgroup waits for no other, but counts for those that come after it.
+  hipError_t enter(const void *owner, int tiles, int cus, hipStream_t s, int32_t *near);
+  // After the launches.  waits: the owner calls done() once it has waited for them.
+  hipError_t leave(const void *owner, bool waits);
+  void done(const void *owner);
+  std::mutex mu;             // held by the caller from enter() to leave(), and around done()
+
+ private:
+  struct Run {
+    const void *owner;
+    int need;
+    hipStream_t stream;
+    // After the launches, once recorded: by leave(), or, if the owner waits, by the first that
+    // has to wait for it (an event in every solve would cost it more than this list).
+    hipEvent_t ev;
+    bool recorded;
+  };
+  hipError_t after(Run &r);
+  std::vector<Run> runs_;    // that may not have ended, oldest first
 };
 constexpr int kMaxDevices = 64;
 TeamTurn &team_turn(int device);

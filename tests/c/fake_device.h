@@ -83,6 +83,7 @@ inline void reset() {
   memset(steps, 0, sizeof(steps));
 }
 inline int count(const char *what) {
+  std::lock_guard<std::recursive_mutex> lk(mu);
   int n = 0;
   for (const std::string &s : log) n += s == what;
   return n;

@@ -2,7 +2,10 @@
 // Usage: host_paths <scenario>; prints what went wrong and returns 1, or "ok".
 #include "fake_device.h"
 
+#include <chrono>
+#include <condition_variable>
 #include <string>
+#include <thread>
 
 using namespace plcg;
 
@@ -136,12 +139,102 @@ void step_counts(bool lose) {
   }
 }
 
+// While a solve's team launch is on the GPU: a solve of one workgroup ends, a batch step
+// returns, another solve that fits beside it waits for nothing, and one that does not is made
+// to wait on the GPU, after the event of the first.
+void turns() {
+  fake::reset();
+  fake::converge_t = 100;
+  const hipStream_t slow = reinterpret_cast<hipStream_t>(vec(1));
+  struct Solve {
+    plcg_handle *h;
+    double *b, *x;
+    hipStream_t s;
+    plcg_result r{};
+    std::atomic<bool> done{false};
+    std::thread th;
+    void start() {
+      th = std::thread([this]() {
+        plcg_solve(h, b, x, 1e-8, 1000, s, &r);
+        done = true;
+      });
+    }
+  };
+  auto make = [](Solve &v, int nx, int ny, int l, hipStream_t s) {
+    v.h = solver(nx, ny, PLCG_METHOD_PLCG, l);
+    v.b = vec((size_t)nx * ny);
+    v.x = vec((size_t)nx * ny);
+    v.s = s;
+  };
+  auto soon = [](const std::function<bool()> &f) {
+    for (int k = 0; k < 2000 && !f(); ++k) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    return f();
+  };
+  Solve a, one, small, large;
+  make(a, 1024, 1024, 1, slow);          // 224 tiles
+  make(one, 60, 40, 2, nullptr);         // one
+  make(small, 100, 80, 2, nullptr);
+  make(large, 1024, 1000, 1, nullptr);
+  double *v = vec(10000);
+  plcg_batch *b = make_batch(2, 2, 0);
+  add(b, 100, 100, v, 1000);
+  plcg_batch_step(b, 4, nullptr);        // set up
+  (void)hipStreamSynchronize(nullptr);
+  // the slow stream's wait for its team launch does not end until it may
+  std::atomic<bool> waiting{false}, may_end{false};
+  fake::on_sync = [&](hipStream_t s) {
+    if (s != slow || fake::count("team") == 0) return;
+    waiting = true;
+    while (!may_end) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  };
+  a.start();
+  EXPECT(soon([&]() { return waiting.load(); }), "the first solve did not start");
+  one.start();
+  EXPECT(soon([&]() { return one.done.load(); }), "a solve of one workgroup waits");
+  EXPECT(fake::count("wait") == 0, "%d waits", fake::count("wait"));
+  std::atomic<bool> stepped{false};
+  std::thread step([&]() {
+    plcg_batch_step(b, 16, nullptr);
+    stepped = true;
+  });
+  EXPECT(soon([&]() { return stepped.load(); }), "a batch step waits on the host");
+  small.start();
+  EXPECT(soon([&]() { return small.done.load(); }), "a small solve waits on the host");
+  EXPECT(fake::count("wait") == 0, "%d waits", fake::count("wait"));
+  large.start();
+  EXPECT(soon([&]() { return large.done.load(); }), "a large solve waits on the host");
+  EXPECT(fake::count("wait") >= 1, "%d waits", fake::count("wait"));
+  may_end = true;
+  a.th.join();
+  one.th.join();
+  small.th.join();
+  large.th.join();
+  step.join();
+  for (Solve *s : {&a, &one, &small, &large})
+    EXPECT(s->r.reason == PLCG_REASON_CONVERGED && s->r.iters == 100, "reason %d after %d",
+           s->r.reason, s->r.iters);
+  fake::on_sync = nullptr;
+  plcg_batch_destroy(b);
+  // of any launches that may run at once what they need fits, whatever came and went before
+  srand(5);
+  for (int round = 0; round < 20000; ++round) {
+    int needs[8], n = rand() % 8, per = 1 + rand() % 32, need = 1 + rand() % 32;
+    for (int k = 0; k < n; ++k) needs[k] = 1 + rand() % per;
+    const int first = team_beside(needs, n, need, per);
+    int sum = need;
+    for (int k = first; k < n; ++k) sum += needs[k];
+    EXPECT(first == n || sum <= per, "%d of %d", sum, per);
+    EXPECT(first == 0 || sum + needs[first - 1] > per, "waits for one that fits");
+  }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "lost_record") lost_record();
   else if (name == "step_counts") step_counts(false);
+  else if (name == "turns") turns();
   else if (name == "step_counts_lost") step_counts(true);
   else {
     printf("unknown scenario %s\n", name.c_str());
