@@ -511,7 +511,7 @@ int32_t run_plain(plcg_batch *b, int ticks, hipStream_t st, bool team) {
     hipGraph_t g;
     int64_t saved = b->tick;
     hipError_t he = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-    int32_t e = he == hipSuccess ? launch_ticks(b, kGraphTicks, cap, !b->rounds.empty()) : PLCG_E_HIP;
+    int32_t e = he == hipSuccess ? launch_ticks(b, kGraphTicks, cap, team) : PLCG_E_HIP;
     hipError_t he2 = hipStreamEndCapture(cap, &g);
     b->tick = saved;
     (void)hipStreamDestroy(cap);
@@ -562,11 +562,12 @@ int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
   if (b->sched.empty()) return PLCG_OK;
   if (!b->rounds.empty()) {
     // In a caller's capture the ticks run all sweeps: a replayed launch's tags would
-    // not be new, and nothing would keep it apart from other team launches.
+    // not be new, and nothing would keep it apart from other team launches.  (The batch's own
+    // graph holds ticks that leave the sweeps to team launches.)
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
       (void)hipGetLastError();
-      return run_plain(b, ticks, st, false);
+      return launch_ticks(b, ticks, st, false);
     }
     const bool lean = b->team_only && !any_solo(b);
     int lead = std::min(ticks, b->setup_left);

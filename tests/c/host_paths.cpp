@@ -228,6 +228,34 @@ void turns() {
   }
 }
 
+// A step in a caller's capture: its replays move every system by as many steps, whether the
+// batch replays groups of ticks from a graph of its own or not.
+void capture() {
+  double *v = vec(40000);
+  for (int use_graph : {0, 1})
+    for (int built : {0, 1}) {
+      fake::reset();
+      const hipStream_t s = reinterpret_cast<hipStream_t>(v);
+      plcg_batch *b = make_batch(2, 4, use_graph);
+      add(b, 100, 80, v, 1000, s);
+      add(b, 1, 3000, v, 1000, s);
+      plcg_batch_step(b, built ? 40 : 6, s);       // built: with its own graph in place
+      (void)hipStreamSynchronize(s);
+      fake::capturing = s;
+      EXPECT(plcg_batch_step(b, 20, s) == PLCG_OK, "%s", plcg_last_error());
+      fake::capturing = nullptr;
+      EXPECT(fake::capture_faults == 0, "%d calls that a capture forbids", fake::capture_faults);
+      for (int replay = 0; replay < 3; ++replay) {
+        memset(fake::steps, 0, sizeof(fake::steps));
+        for (fake::Work &w : fake::captured) w();
+        for (int k = 0; k < 2; ++k)
+          EXPECT(fake::steps[k] == 20, "use_graph %d: system %d made %d of 20 steps", use_graph, k,
+                 fake::steps[k]);
+      }
+      plcg_batch_destroy(b);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -235,6 +263,7 @@ int main(int argc, char **argv) {
   if (name == "lost_record") lost_record();
   else if (name == "step_counts") step_counts(false);
   else if (name == "turns") turns();
+  else if (name == "capture") capture();
   else if (name == "step_counts_lost") step_counts(true);
   else {
     printf("unknown scenario %s\n", name.c_str());
