@@ -947,17 +947,22 @@ plcg_status plcg_batch_autotune(plcg_batch *b, int32_t ticks, void *stream) {
     b->dirty = true;
     return PLCG_OK;
   };
-  // Time `ticks` launches of the live batch under the current choice, per active
-  // unknown (systems that finish between trials shrink the work of later ones).
+  // Time `ticks` ticks of the live batch under the current choice, per active
+  // unknown (systems that finish between trials shrink the work of later ones).  The team
+  // launches, which the choice does not change, make their sweeps ahead of them.
   auto trial = [&](double *cost) -> int32_t {
     int32_t e = apply();
     if (e == PLCG_OK) e = run_ticks(b, 2, st);   // settle: the new partial count reaches the owners
     if (e != PLCG_OK) return e;
     int64_t active = 0;
     for (size_t s = 0; s < b->slots.size(); ++s)
-      if (b->in_use[s] && b->reports[s].phase != kDone) active += b->slots[s].n;
+      if (b->in_use[s] && b->reports[s].phase != kDone &&
+          (b->slots[s].team == 0 || b->rounds.empty() || b->reports[s].solo != 0))
+        active += b->slots[s].n;
+    const bool team = !b->rounds.empty();
+    if (team && (e = launch_rounds(b, ticks, st)) != PLCG_OK) return e;
     BHIP(hipEventRecord(e0, st));
-    if ((e = run_ticks(b, ticks, st)) != PLCG_OK) return e;
+    if ((e = run_plain(b, ticks, st, team)) != PLCG_OK) return e;
     BHIP(hipEventRecord(e1, st));
     BHIP(hipEventSynchronize(e1));
     float ms = 0.f;

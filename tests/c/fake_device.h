@@ -24,7 +24,7 @@ using Work = std::function<void()>;
 
 inline std::recursive_mutex mu;
 inline std::vector<Work> queue;                  // all streams, in the order of the calls
-inline std::vector<std::string> log;             // launches and event records
+inline std::vector<std::string> log;             // launches, event records (of a timing event: time), waits
 inline std::function<void(hipStream_t)> on_sync; // before a stream is waited for
 inline std::function<bool(size_t)> refuse;       // allocations that fail
 inline hipStream_t capturing = nullptr;          // the caller's stream in capture
@@ -171,17 +171,17 @@ hipError_t hipDeviceSynchronize(void) {
   fake::drain();
   return hipSuccess;
 }
-hipError_t hipEventCreate(hipEvent_t *e) {
-  *e = reinterpret_cast<hipEvent_t>(malloc(8));
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned flags) {
+  *e = reinterpret_cast<hipEvent_t>(new unsigned(flags));
   return hipSuccess;
 }
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) {
-  free(e);
+  delete reinterpret_cast<unsigned *>(e);
   return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) {
-  fake::note("record");
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+  fake::note(*reinterpret_cast<unsigned *>(e) & hipEventDisableTiming ? "record" : "time");
   return hipSuccess;
 }
 hipError_t hipEventQuery(hipEvent_t) {

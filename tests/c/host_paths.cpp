@@ -256,6 +256,36 @@ void capture() {
     }
 }
 
+// The schedule's tuner times the launches that its candidates change and nothing else, and
+// moves the systems that team launches sweep meanwhile.
+void autotune() {
+  fake::reset();
+  double *v = vec(40000);
+  plcg_batch *b = make_batch(2, 4, 0);
+  add(b, 100, 80, v, 100000);
+  add(b, 1, 3000, v, 100000);
+  EXPECT(plcg_batch_autotune(b, 8, nullptr) == PLCG_OK, "%s", plcg_last_error());
+  (void)hipStreamSynchronize(nullptr);
+  bool timed = false;
+  int trials = 0, slots = 0, ticks = 0;
+  for (const std::string &s : fake::log) {
+    if (s == "time") {
+      timed = !timed;
+      trials += timed;
+    }
+    if (timed) {
+      slots += s == "slots";
+      ticks += s == "tick";
+    }
+  }
+  EXPECT(trials == 20 && ticks == 8 * trials, "%d trials, %d timed ticks", trials, ticks);
+  EXPECT(slots == 0, "%d team launches within the timed ticks", slots);
+  for (int k = 0; k < 2; ++k)
+    EXPECT(fake::steps[k] >= trials * 10, "system %d made %d steps in %d trials of 8 + 2", k,
+           fake::steps[k], trials);
+  plcg_batch_destroy(b);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -264,6 +294,7 @@ int main(int argc, char **argv) {
   else if (name == "step_counts") step_counts(false);
   else if (name == "turns") turns();
   else if (name == "capture") capture();
+  else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
   else {
     printf("unknown scenario %s\n", name.c_str());
