@@ -1465,11 +1465,16 @@ plcg_status plcg_create(const plcg_operator_desc *op, const plcg_config *cfg, pl
   if (e == PLCG_OK && h->var) e = copy_var(h, op);
   if (e == PLCG_OK) e = finish_setup(h, op, cfg, res_ok);
   if (e == PLCG_OK && h->team) {
+    // without memory for the mail the solver has its other kernels
     const size_t bytes = team_post_bytes() + team_mail_bytes(h->team_geom);
-    e = dev_alloc(h, &h->team_post, bytes);
-    h->team_mail = static_cast<char *>(h->team_post) + team_post_bytes();
-    if (e == PLCG_OK && hipMemsetAsync(h->team_post, 0, bytes, nullptr) != hipSuccess)
-      e = fail(PLCG_E_HIP, "clearing the team mail failed");
+    if (dev_alloc(h, &h->team_post, bytes) != PLCG_OK) {
+      (void)hipGetLastError();
+      h->team = false;
+    } else {
+      h->team_mail = static_cast<char *>(h->team_post) + team_post_bytes();
+      if (hipMemsetAsync(h->team_post, 0, bytes, nullptr) != hipSuccess)
+        e = fail(PLCG_E_HIP, "clearing the team mail failed");
+    }
   }
   if (e != PLCG_OK) {
     release(h);

@@ -286,6 +286,27 @@ void autotune() {
   plcg_batch_destroy(b);
 }
 
+// On a device with no room for the mail of team launches, a solver is made, and streams (or runs
+// resident), as it did before it had any.
+void no_mail() {
+  for (int n : {64, 200}) {
+    fake::reset();
+    fake::converge_t = 100;
+    TeamGeom g;
+    EXPECT(team_plan(1, 2, false, false, n, n, 1, 256, &g), "no plan");
+    const size_t mail = team_post_bytes() + team_mail_bytes(g);
+    fake::refuse = [mail](size_t bytes) { return bytes == mail; };
+    plcg_handle *h = solver(n, n, PLCG_METHOD_PLCG, 2);
+    if (h == nullptr) return;
+    double *b = vec((size_t)n * n), *x = vec((size_t)n * n);
+    plcg_result r{};
+    EXPECT(plcg_solve(h, b, x, 1e-8, 1000, nullptr, &r) == PLCG_OK, "%s", plcg_last_error());
+    EXPECT(r.iters == 100 && r.reason == PLCG_REASON_CONVERGED, "%d", r.iters);
+    EXPECT(fake::count("team") == 0, "%d", fake::count("team"));
+    plcg_destroy(h);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -294,6 +315,7 @@ int main(int argc, char **argv) {
   else if (name == "step_counts") step_counts(false);
   else if (name == "turns") turns();
   else if (name == "capture") capture();
+  else if (name == "no_mail") no_mail();
   else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
   else {

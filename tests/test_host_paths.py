@@ -30,7 +30,8 @@ def exe(tmp_path_factory):
     return str(out)
 
 
-@pytest.mark.parametrize("scenario", ["lost_record", "step_counts", "step_counts_lost", "turns", "capture", "autotune"])
+@pytest.mark.parametrize("scenario", ["lost_record", "step_counts", "step_counts_lost", "turns", "capture", "autotune",
+                                      "no_mail"])
 def test_host_path(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
