@@ -14,9 +14,9 @@
 // launch starts or ends: the products of a launch's last sweep are summed as within
 // it and kept in the slot's state (BatchState::raw).
 //
-// A launch either advances a system by all of its sweeps or leaves it as it was: its tiles
-// store their vectors, and tile 0 the state, only once all have made their last sweep and the
-// slot's word says so (SlotRun::settle; 1 us or so once per launch).
+// A launch either advances a system by all of its sweeps or leaves it as it was: no tile
+// stores its vectors, and tile 0 not the state, before it is sure that none gives the run up
+// (`stands` in team_sweeps).
 #include "plcg_batch_phase.h"
 #include "plcg_team_kernels.h"
 
@@ -37,17 +37,6 @@ struct SlotRun {
   __device__ inline int first() const { return i0; }
   __device__ inline int post_offset() const { return post_off; }
   __device__ inline int32_t *lost(const TeamArgs &) const { return lost_word; }
-  // What the launch of first tag `base` comes to for this slot: lost (base) or whole (-base),
-  // whichever is settled first.  Returns it.  (A loss that some tiles saw and others did not
-  // would leave vectors of different sweeps.)
-  __device__ inline int settle(int base, int mine) const {
-    int old = __hip_atomic_load(lost_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (old != base && old != -base) {
-      const int seen = atomicCAS(lost_word, old, mine);
-      old = seen == old ? mine : seen;
-    }
-    return old;
-  }
   __device__ inline double *vec(int k) const { return S->vec + (size_t)k * S->vstride; }
 
   // Coefficients of the sweeps t whose columns earlier launches finalised, as

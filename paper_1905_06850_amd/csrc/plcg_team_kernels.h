@@ -43,6 +43,7 @@ using rsrc_t = __amdgpu_buffer_rsrc_t;
 constexpr int kAgentScope = 16;              // cache policy bit sc1 of the buffer accesses
 constexpr long long kStartTicks = 25000000;  // 0.25 s of the 100 MHz clock: first waits of a run
 constexpr long long kWaitTicks = 200000000;  // 2 s: any later one
+constexpr long long kLastTicks = 2000000000; // 20 s: one that all workgroups are known to answer
 constexpr int kNever = 0x7fffffff;
 
 __device__ inline rsrc_t mail_rsrc(void *p, int bytes) {
@@ -86,9 +87,9 @@ struct Patience {
   long long t0, limit;
   int spins;
   bool gone;                     // a sum was given up
-  __device__ inline void reset(bool start) {
+  __device__ inline void reset(bool start, long long later = kWaitTicks) {
     spins = 0;
-    limit = start ? kStartTicks : kWaitTicks;
+    limit = start ? kStartTicks : later;
   }
   // after a poll that did not find its word
   __device__ inline bool over() {
@@ -649,8 +650,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       spoil_products(red[1]);
     }
     if constexpr (SLOT) gone = 1;
-    if constexpr (SLOT) run.settle(a.base, a.base);
-    else __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(lost, a.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   // Whether sweep i does not run.  A batched system's launch ends after sweep iend, but
   // not between the column that stops the solve and its last sweep.
@@ -658,6 +658,18 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     const int at = stop_at;
     return at <= i || (SLOT && i > a.imax && at == kNever);
   };
+
+  // SLOT: whether the run surely stands once it has ended before sweep i, for everybody, so
+  // that a workgroup may store its vectors at once.  It does after two sums of the launch:
+  // every workgroup has made the first then, so all are on the GPU, and the waits after it end
+  // for no time that they take, only if the run is lost already.  Otherwise everybody waits for
+  // the products of the last sweep: a workgroup that gave up before has not posted any, and
+  // if one has not begun, its neighbours wait for its faces in vain.
+  auto stands = [&](int i) {
+    const int at = stop_at;
+    return tiles == 1 || (at - L < i - 1 ? at - L : i - 1) - i0 >= 2;
+  };
+  constexpr long long kLater = SLOT ? kLastTicks : kWaitTicks;
 
   if (wave == 0) {
     const rsrc_t post = mail_rsrc(a.post, (int)(team_post_bytes() - run.post_offset()));
@@ -671,32 +683,10 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       EngineIn<L> in;
       double raw[ND];
       if constexpr (L >= 3) in = engine_gather<L>(sh, c);
-      auto sum = [&]() {
-        return team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat,
-                            [&]() {
-                              if constexpr (L < 3) in = engine_gather<L>(sh, c);
-                            });
-      };
-      // SLOT, over: everybody's last sweep is made, and the run stands, unless a workgroup that
-      // did not see that in time has given it up first.  One that did not, of a run that
-      // stands, looks again: everything it waits for is there.
-      auto settled_sum = [&](const auto &run) {
-        for (int tries = 0;; ++tries) {
-          const bool ok = sum();
-          if (!over || tiles == 1) return ok;
-          int fate = 0;
-          if (lane == 0) fate = run.settle(a.base, ok ? -a.base : a.base);
-          if (__builtin_amdgcn_readfirstlane(fate) == a.base) return false;
-          if (ok || tries == 1) return ok;
-          pat.reset(false);
-          pat.gone = false;
-        }
-      };
-      bool lost_sum;
-      if constexpr (SLOT) lost_sum = !settled_sum(run);
-      else lost_sum = !sum();
-      if (lost_sum) {
-        if (lane == 0) lose(at);
+      if (!team_sum<ND>(post, c, base + (unsigned)c, tiles, LAG ? own_before : own, raw, pat, [&]() {
+            if constexpr (L < 3) in = engine_gather<L>(sh, c);
+          })) {
+        if (lane == 0) lose(over ? kNever : at);
         running = false;
         return;
       }
@@ -727,19 +717,19 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
     __syncthreads();
     int i = i0;
     for (; SLOT || i <= a.imax; ++i) {
-      // SLOT, over: everybody posts and collects the products of the last sweep, of which
-      // the next launch makes column i: then all have read the state that tile 0 rewrites,
-      // and the run is settled before anybody stores a vector.
-      const bool over = SLOT && ended(i);
-      pat.reset(i - i0 <= 1 + LAG);
+      // SLOT, over: everybody posts the products of the last sweep, of which the next
+      // launch makes column i, and tile 0 collects them, so that it rewrites the state
+      // only after all the others have read it; all do where the run may not stand.
+      const bool over = SLOT && ended(i), ask = over && !stands(i);
+      pat.reset(!over && i - i0 <= 1 + LAG, kLater);
       if (i >= (SLOT ? i0 + 1 : 1) && (running || (over && !gone))) {
         own_before = own;
         own = own_products<ND>(red[(i - 1) & 1]);
         if (tiles > 1) post_products<ND>(post, own, i, tile, base + (unsigned)i);
-        if (i > LAG) column(i - LAG, L == 1 ? i : i + 1, over);
+        if (i > LAG && (!over || ask || tile == 0)) column(i - LAG, L == 1 ? i : i + 1, over);
       }
       if (SLOT && over) {
-        if (tiles > 1) __syncthreads();
+        if (ask) __syncthreads();
         break;
       }
       if (L == 1) __syncthreads();
@@ -754,8 +744,9 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
   } else if (SLOT && wave > nw) {
     // waves that this system does not need keep the barriers
     __syncthreads();
-    for (int i = i0; !ended(i); ++i) __syncthreads();
-    if (tiles > 1) __syncthreads();
+    int i = i0;
+    for (; !ended(i); ++i) __syncthreads();
+    if (!stands(i)) __syncthreads();
   } else {
     OP op(a, tile, tiles, wave - 1, ops);
     static_assert(R == 2, "z_i and z_{i-1}");
@@ -807,7 +798,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       typename OP::Words words;
       double s[V];
       if (L >= 2 && ended(i)) break;
-      pat.reset(i - i0 <= 1);
+      pat.reset(i - i0 <= 1, kLater);
       op.request(i, words);
       auto neighbours = [&]() {
         if (!op.sums(i, tag, zl[0], words, s, pat)) lose(L == 1 ? i : i + 1);
@@ -904,7 +895,7 @@ __device__ __forceinline__ void team_sweeps(const TeamArgs &a, const RUN &run) {
       __syncthreads();
     }
     if constexpr (SLOT) {
-      if (tiles > 1) __syncthreads();      // the run is settled
+      if (!stands(i)) __syncthreads();     // it does now, or it is lost
       if (!gone) {
         const bool over = stop_at <= i || i - L > run.m;
 #pragma unroll
