@@ -228,6 +228,23 @@ void turns() {
   }
 }
 
+// A step of one tick costs a team launch beside its tick: it makes two sweeps for them.
+void single_ticks() {
+  fake::reset();
+  double *v = vec(10000);
+  plcg_batch *b = make_batch(2, 1, 0);
+  add(b, 100, 80, v, 1000);
+  plcg_batch_step(b, 4, nullptr);
+  (void)hipStreamSynchronize(nullptr);
+  fake::log.clear();
+  memset(fake::steps, 0, sizeof(fake::steps));
+  for (int k = 0; k < 10; ++k) plcg_batch_step(b, 1, nullptr);
+  (void)hipStreamSynchronize(nullptr);
+  const int launches = fake::count("slots") + fake::count("tick");
+  EXPECT(fake::steps[0] >= launches, "%d sweeps in %d launches", fake::steps[0], launches);
+  plcg_batch_destroy(b);
+}
+
 // A step in a caller's capture: its replays move every system by as many steps, whether the
 // batch replays groups of ticks from a graph of its own or not.
 void capture() {
@@ -316,6 +333,7 @@ int main(int argc, char **argv) {
   else if (name == "turns") turns();
   else if (name == "capture") capture();
   else if (name == "no_mail") no_mail();
+  else if (name == "single_ticks") single_ticks();
   else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
   else {
