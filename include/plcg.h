@@ -90,7 +90,8 @@ enum { PLCG_PREC_FP64 = 0, PLCG_PREC_FP32_REFINED = 1 };
  *   of the constant and the Jacobi-scaled variable stencils from 1536 to about a million
  *   unknowns (CG, p(1) .. p(3), x_update AUTO, at most 2^20 iterations) and of CSR matrices
  *   with up to nine entries per row and 490 thousand rows (250 thousand beyond five
- *   entries; p(1) .. p(3)), one launch per run of up to one workgroup per CU, the vectors
+ *   entries; p(1) .. p(3); not where the order of 24 to 250 thousand rows scatters their
+ *   columns), one launch per run of up to one workgroup per CU, the vectors
  *   in their registers and the workgroups exchanging what their neighbours need and the
  *   products inside the launch.  It gives up without effect when other work keeps its workgroups
  *   from running all at once, and the run is then made by the other kernels.  Reported

@@ -225,6 +225,7 @@ struct plcg_handle {
   int res_kind = -1;              // operator kind of the resident kernels; -1: streaming
   bool team = false;              // segments run as team launches
   int cus = 0;                    // of the device
+  double rows_lines = 0.0;        // team_rows_lines of the matrix
   TeamGeom team_geom{};
   void *team_mail = nullptr, *team_post = nullptr;
   int team_base = 1;              // first tag of the next team launch
@@ -1099,6 +1100,7 @@ plcg_status copy_csr(plcg_handle *h, const plcg_operator_desc *op) {
     }
     ci.swap(eci);
     va.swap(eva);
+    if (kmax <= kRowsLong) h->rows_lines = team_rows_lines(ci.data(), h->n, (int)kmax, (int)ld);
   }
   const size_t stored = ell ? (size_t)kmax * ld : nnz;
   int64_t *drp = nullptr;
@@ -1375,7 +1377,7 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
   // at 100 x 37: its two sums wait for other workgroups.
   const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
   const bool rows = op->kind == PLCG_OP_CSR && pl && h->l <= kTeamLMax && h->od.ell_k > 0 &&
-                    h->res_kind < 0;
+                    h->res_kind < 0 && team_rows_pays((int)n, h->l, h->rows_lines);
   int &cus = h->cus;
   if (cfg->launch_mode == PLCG_LAUNCH_AUTO && xu == PLCG_X_AUTO &&
       h->precision == PLCG_PREC_FP64 && ((stencil && (!h->var || h->jacobi)) || rows) &&

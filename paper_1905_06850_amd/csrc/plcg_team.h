@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #if defined(__HIP__)
 #define PLCG_HD __host__ __device__
 #else
@@ -263,6 +265,42 @@ inline bool team_rows_plan(int n, int k, int tiles, TeamGeom *out) {
   g.words = 2 * g.wz * 64 * v;       // four copies of the unknowns' words, where faces have two
   *out = g;
   return team_mail_bytes(g) <= kTeamMailMax;
+}
+
+// Mean number of 128-byte lines of words that one gather of a wave touches, 64 rows' j-th
+// entries (ELL: entry j of row p at j * ld + p): 8 where neighbours of consecutive rows are
+// consecutive, 64 where the order of the rows says nothing.  From up to 256 waves.
+inline double team_rows_lines(const int32_t *ci, int n, int k, int ld) {
+  if (n < 1 || k < 1) return 0.0;
+  const int waves = (n - 1) / 64 + 1, step = (waves - 1) / 256 + 1;
+  std::vector<int32_t> seen((size_t)(n - 1) / 8 + 1, -1);
+  int32_t gathers = 0;
+  long long lines = 0;
+  for (int w = 0; w < waves; w += step)
+    for (int j = 0; j < k; ++j, ++gathers)
+      for (int p = 64 * w; p < n && p < 64 * w + 64; ++p) {
+        int32_t &s = seen[(size_t)ci[(size_t)j * ld + p] / 8];
+        lines += s != gathers;
+        s = gathers;
+      }
+  return (double)lines / gathers;
+}
+// Whether the team launches' gathers of words, twice as wide as the streaming kernels' and
+// from beyond the L1 caches, leave them faster for rows of this order.  us per iteration,
+// team / streaming, rows of a five-point grid shuffled within 256, 1024, 4096 rows and all
+// (about 27, 43, 51 and 55 lines a gather; as the grid's, 9):
+//   p(1)  40 000 3.8 / 6.2,  6.1 / 6.6, 7.4 / 6.8, 8.2 / 8.0;   119 700 -, 6.7 / 6.8, 7.9 / 7.0,
+//         8.7 / 9.1;   240 100 -, 7.2 / 8.2, 8.5 / 8.9, 10.0 / 12.5
+//   p(2)  22 500 -, 5.1 / 5.6, -, 6.2 / 6.9;   40 000 4.2 / 5.3, 6.7 / 5.7, 8.0 / 6.0, 8.8 / 7.1;
+//         119 700 -, 7.3 / 6.1, -, 9.1 / 8.3;   230 400 5.6 / 7.2, 7.8 / 7.5, 8.5 / 8.0, 9.5 / 12.0;
+//         260 100 5.6 / 8.1, 8.0 / 8.4, 8.6 / 8.9, 10.6 / 13.0
+//   p(2), seven entries, 15 000 -, 5.6 / 6.3, -, 6.6 / 7.7;   27 000 -, 6.9 / 6.5, -, 8.6 / 8.1;
+//         241 800 6.8 / 9.2, 9.3 / 9.4, 10.7 / 10.1, 10.6 / 14.9
+// and p(3) as p(2).  The lines are drawn where rows shuffled within a part of the matrix, as an
+// unstructured mesh numbers them, begin and cease to be slower.
+inline bool team_rows_pays(int n, int l, double lines) {
+  return l == 1 ? lines <= 47.0 || n < 24000 || n > 150000
+                : lines <= 35.0 || n < 24000 || n > 250000;
 }
 
 }  // namespace plcg

@@ -2,6 +2,7 @@
 // Usage: host_paths <scenario>; prints what went wrong and returns 1, or "ok".
 #include "fake_device.h"
 
+#include <algorithm>
 #include <chrono>
 #include <condition_variable>
 #include <string>
@@ -245,6 +246,75 @@ void single_ticks() {
   plcg_batch_destroy(b);
 }
 
+// The five-point matrix of a side x side grid, its rows shuffled within blocks of `block`
+// (1: not): whether a solve runs in a team launch.
+bool rows_team(int side, int block, int l) {
+  const int n = side * side;
+  std::vector<int> at(n);
+  for (int k = 0; k < n; ++k) at[k] = k;
+  for (int b0 = 0; b0 < n; b0 += block)
+    for (int k = std::min(n, b0 + block) - 1; k > b0; --k) std::swap(at[k], at[b0 + rand() % (k - b0 + 1)]);
+  std::vector<std::vector<int>> cols(n);
+  for (int k = 0; k < n; ++k) {
+    const int x = k % side, y = k / side;
+    std::vector<int> &c = cols[at[k]];
+    c.push_back(at[k]);
+    if (x > 0) c.push_back(at[k - 1]);
+    if (x < side - 1) c.push_back(at[k + 1]);
+    if (y > 0) c.push_back(at[k - side]);
+    if (y < side - 1) c.push_back(at[k + side]);
+  }
+  std::vector<int64_t> rp(1, 0);
+  std::vector<int32_t> ci;
+  std::vector<double> va;
+  for (std::vector<int> &c : cols) {
+    std::sort(c.begin(), c.end());
+    for (int j : c) {
+      ci.push_back(j);
+      va.push_back(1.0);
+    }
+    rp.push_back((int64_t)ci.size());
+  }
+  fake::reset();
+  fake::converge_t = 100;
+  plcg_operator_desc op{};
+  op.kind = PLCG_OP_CSR;
+  op.nx = n;
+  op.ny = op.nz = 1;
+  op.nnz = (int64_t)ci.size();
+  op.rowptr = rp.data();
+  op.colind = ci.data();
+  op.vals = va.data();
+  plcg_config cfg{};
+  cfg.method = PLCG_METHOD_PLCG;
+  cfg.l = l;
+  cfg.lambda_max = 8.0;
+  cfg.max_restarts = -1;
+  plcg_handle *h = nullptr;
+  EXPECT(plcg_create(&op, &cfg, &h) == PLCG_OK, "%s", plcg_last_error());
+  double *b = vec(n), *x = vec(n);
+  plcg_result r{};
+  EXPECT(plcg_solve(h, b, x, 1e-8, 1000, nullptr, &r) == PLCG_OK, "%s", plcg_last_error());
+  plcg_destroy(h);
+  return fake::count("team") > 0;
+}
+
+// Matrices whose rows are in an order that scatters their gathers stream where that is faster.
+void rows_order() {
+  const struct {
+    int side, block, l;
+    bool team;
+  } cases[] = {{200, 1, 1, true},   {200, 1, 3, true},     {200, 64, 2, true},
+               {200, 256, 2, true}, {200, 1024, 1, true},  {200, 1024, 2, false},
+               {200, 1024, 3, false}, {200, 4096, 1, false}, {200, 40000, 1, false},
+               {200, 40000, 2, false}, {150, 22500, 2, true}, {346, 1024, 2, false},
+               {346, 1024, 1, true}, {346, 4096, 1, false}, {490, 240100, 1, true},
+               {510, 260100, 2, true}};
+  for (const auto &c : cases)
+    EXPECT(rows_team(c.side, c.block, c.l) == c.team, "%d^2 rows shuffled within %d, p(%d): %s",
+           c.side, c.block, c.l, c.team ? "streams" : "team launch");
+}
+
 // A step in a caller's capture: its replays move every system by as many steps, whether the
 // batch replays groups of ticks from a graph of its own or not.
 void capture() {
@@ -333,6 +403,7 @@ int main(int argc, char **argv) {
   else if (name == "turns") turns();
   else if (name == "capture") capture();
   else if (name == "no_mail") no_mail();
+  else if (name == "rows_order") rows_order();
   else if (name == "single_ticks") single_ticks();
   else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
