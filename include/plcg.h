@@ -205,12 +205,16 @@ typedef struct {
   int32_t host_waits;     /* plcg_solve: times the host blocked on the device (stream and
                              event synchronisations): about (iterations + l) / check_every
                              plus a few per restart or refinement step (STREAMING), a few
-                             per restart (RESIDENT); 0 from batches */
+                             per restart (launches that run many iterations); 0 from
+                             batches */
   int32_t launch_mode;    /* PLCG_LAUNCH_STREAMING or PLCG_LAUNCH_RESIDENT: how the
-                             iterations of this solve ran (0 from batches) */
+                             iterations of this solve ran, a launch of up to one workgroup
+                             per CU (see PLCG_LAUNCH_AUTO) counting as the mode that AUTO
+                             otherwise has for the size (0 from batches) */
   int32_t x_update_every; /* 2: the streaming sweeps of this solve wrote x on every
                              second iteration (PLCG_X_PAIRED), 1: on every iteration
-                             (also resident launches); 0 from batches */
+                             (also all launches that run many iterations); 0 from
+                             batches */
 } plcg_result;
 
 /* Create a solver for one operator and one configuration.
@@ -270,7 +274,8 @@ plcg_status plcg_get_history(const plcg_handle *h, double *out, int32_t cap, int
  * around each group of check_every back-to-back launches; reported in
  * plcg_result.sweep_ms / sweeps, summed over the groups in which every launch
  * did work (over every group with work when a solve is shorter than a group).
- * A RESIDENT solve times each of its launches and counts in sweeps the
+ * A solve whose launches run many iterations (RESIDENT, and those that AUTO has
+ * beside it) times each of them and counts in sweeps the
  * iteration launches it replaces (p(l)-CG: the sweeps it ran; CG: two per
  * iteration), so sweep_ms / sweeps compares with the STREAMING figure. */
 plcg_status plcg_set_timing(plcg_handle *h, int32_t enable);

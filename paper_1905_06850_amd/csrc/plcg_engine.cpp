@@ -233,6 +233,7 @@ struct plcg_handle {
   int sweep_nb[2] = {0, 0};       // streaming workgroups of the FP32 / FP64-stored sweeps (0: not chosen yet)
   bool pair64 = false, pair32 = false;   // the same sweeps update x on even t only
   bool ran_resident = false;      // the current solve ran resident launches
+  bool ran_team = false;          // ... team launches, and no others
   OpData od{nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, nullptr};   // library copies of the operator data
   bool var = false;               // variable-coefficient stencil (edge weights in od.sx/sy/sz)
   bool jacobi = false;            // CSR / variable stencil solved in Jacobi-scaled form D^{-1/2} A D^{-1/2}
@@ -531,7 +532,7 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   }
   if (hstat(h)->lost == a.base) {
     tl.set_units(tl.launches() - 1, 0);
-    h->team = false;
+    h->team = h->ran_team = false;
     // The lost launch may have left a record of its own; throttle() reads the status
     // before the first streaming sweep has written one.
     hstat(h)->status = kRunning;
@@ -540,6 +541,7 @@ plcg_status run_team(plcg_handle *h, const double *z0, double *x, double *scratc
   PLCG_HIP(launch_copy(scratch, x, h->n, s));
   // reported as the mode that AUTO has for the size
   h->ran_resident = h->res_kind >= 0;
+  h->ran_team = true;
   *ran = true;
   return PLCG_OK;
 }
@@ -979,7 +981,7 @@ plcg_status do_solve(plcg_handle *h, const double *b, double *x, double tol, int
   PLCG_HIP(hipSetDevice(h->device));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   h->host_waits = 0;
-  h->ran_resident = false;
+  h->ran_resident = h->ran_team = false;
   TimedLaunch tl{h, s};
   int final_slot = 1;
   // Jacobi-scaled CSR: solve D^{-1/2} A D^{-1/2} y = D^{-1/2} b for y = D^{1/2} x
@@ -1024,7 +1026,10 @@ plcg_status do_solve(plcg_handle *h, const double *b, double *x, double tol, int
   res.host_waits = h->host_waits;
   res.launch_mode = h->ran_resident ? PLCG_LAUNCH_RESIDENT : PLCG_LAUNCH_STREAMING;
   res.x_update_every =
-      h->ran_resident || (h->precision == PLCG_PREC_FP32_REFINED ? !h->pair32 : !h->pair64) ? 1 : 2;
+      h->ran_resident || h->ran_team ||
+              (h->precision == PLCG_PREC_FP32_REFINED ? !h->pair32 : !h->pair64)
+          ? 1
+          : 2;
   res.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   if (out) *out = res;
   return PLCG_OK;

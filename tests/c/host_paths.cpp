@@ -246,6 +246,23 @@ void single_ticks() {
   plcg_batch_destroy(b);
 }
 
+// How x was updated, as it is reported: on every iteration by a team launch, on every second
+// one by CG's streaming sweeps, which make the run after a lost launch.
+void x_updates() {
+  for (bool lose : {false, true}) {
+    fake::reset();
+    fake::converge_t = 100;
+    fake::lose_team = lose;
+    plcg_handle *h = solver(200, 150, PLCG_METHOD_CG, 1);
+    double *b = vec(30000), *x = vec(30000);
+    plcg_result r{};
+    EXPECT(plcg_solve(h, b, x, 1e-8, 1000, nullptr, &r) == PLCG_OK, "%s", plcg_last_error());
+    EXPECT(r.x_update_every == (lose ? 2 : 1), "lost %d: %d", lose, r.x_update_every);
+    EXPECT(r.launch_mode == PLCG_LAUNCH_STREAMING, "%d", r.launch_mode);
+    plcg_destroy(h);
+  }
+}
+
 // The five-point matrix of a side x side grid, its rows shuffled within blocks of `block`
 // (1: not): whether a solve runs in a team launch.
 bool rows_team(int side, int block, int l) {
@@ -404,6 +421,7 @@ int main(int argc, char **argv) {
   else if (name == "capture") capture();
   else if (name == "no_mail") no_mail();
   else if (name == "rows_order") rows_order();
+  else if (name == "x_updates") x_updates();
   else if (name == "single_ticks") single_ticks();
   else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
