@@ -662,6 +662,15 @@ def working_set(method, l, x_update_every, n, word, op_bytes):
     return vecs * n * word + op_bytes
 
 
+def team_run(r, resident, jacobi):
+    """Whether a solve of at least 64 iterations (a group of launches) ran each segment in one
+    launch of many workgroups: the host then waits for the setup, the launch and the final
+    residual (and before a Jacobi-scaled solve), twice more per restart; streaming, once more
+    for every group."""
+    return (not resident and r.iters >= 64 * (1 + r.restarts) and
+            r.host_waits <= 3 + (1 if jacobi else 0) + 2 * r.restarts)
+
+
 def run_methods(args, plcg, torch, ctx, methods, steps, warmup, tol=None, inner_tol=None):
     """Each method: `warmup` untimed solves, `steps` timed solves (host clock
     around them, device synchronised on both sides), then one solve with HIP
@@ -711,9 +720,15 @@ def run_methods(args, plcg, torch, ctx, methods, steps, warmup, tol=None, inner_
         # vector passes in the storage precision, plus the operator's own data
         # read once per SpMV (FP64 d, or the CSR arrays)
         bytes_iter = passes * word * n + op_bytes
+        resident = r.launch_mode == plcg.PLCG_LAUNCH_RESIDENT
+        team = team_run(r, resident, kind == "2d5var")
+        if team:
+            # x and z_0 (r_0) read once, x written once, the operator's data read once per run
+            runs = (1 + r.restarts) / max(r.iters, 1)
+            passes = 3 * runs
+            bytes_iter = runs * (3 * word * n + op_bytes)
         kernel_us = 1e3 * rt.sweep_ms / max(rt.sweeps, 1)
         kernels_per_iter = 2 if method == "cg" else 1
-        resident = r.launch_mode == plcg.PLCG_LAUNCH_RESIDENT
         wset = working_set(method, l, r.x_update_every, n, word, op_bytes)
         rows[name] = {
             "iters": r.iters, "reason": plcg.REASONS[r.reason], "restarts": r.restarts,
@@ -731,9 +746,9 @@ def run_methods(args, plcg, torch, ctx, methods, steps, warmup, tol=None, inner_
             "spmvs_per_s": r.spmvs * steps / dt,   # p(l)-CG adds l fill/drain SpMVs
             "outer": r.outer,
             "host_waits": r.host_waits,
-            "launch": "resident" if resident else "streaming",
-            # a resident solve is one launch per restart segment
-            "launches_per_iter": ((1 + r.restarts) / max(r.iters, 1)) if resident
+            "launch": "resident" if resident else "team" if team else "streaming",
+            # a resident or team solve is one launch per restart segment
+            "launches_per_iter": ((1 + r.restarts) / max(r.iters, 1)) if resident or team
             else kernels_per_iter,
             "solves_per_s": steps / dt, "steps": steps, "warmup": warmup,
         }
@@ -749,6 +764,20 @@ def roofline(workload, kind, head_method, hr):
     and whether the kernel's working set fits the 256 MiB memory-side cache
     (whose hits the achieved rate then includes)."""
     d3 = 'true' if kind == '3d7' else 'false'
+    if hr["launch"] == "team":
+        # one launch per run, whose vectors stay on the chip: what bounds it is the exchange
+        # between workgroups in every iteration, not the bytes it moves
+        launches = hr["launches_per_iter"]
+        us, bytes_launch = hr["us_per_iter"] / launches, hr["bytes_per_iter"] / launches
+        achieved = bytes_launch / (us * 1e-6) / 1e9
+        return {
+            "bound": "latency", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": achieved / HBM_PEAK_GBS, "traffic": None,
+            "kernel": "cg_team_kernel" if head_method[0] == "cg" else
+            "rows_team_kernel" if kind == "csr" else "plcg_team_kernel",
+            "kernel_us": us, "bytes_per_launch": bytes_launch,
+            "working_set_bytes": hr["working_set_bytes"], "cache_resident": hr["cache_resident"],
+        }
     if head_method[0] == "cg" and hr["launch"] != "resident":
         # two sweeps per iteration (A: 4 passes, B: 5 on average when paired):
         # their mean duration against half the iteration's bytes
