@@ -122,7 +122,8 @@ struct TeamPlace {
 // of LDS.
 // The variable-coefficient stencils' edge weights share the LDS.
 constexpr int team_vmax(int method_plcg, int l, bool d3, bool var) {
-  return var           ? (d3 ? (l == 3 ? 2 : 3) : !method_plcg ? 6 : l == 1 ? 4 : 3)
+  return method_plcg && l > kTeamLMax ? 0
+         : var         ? (d3 ? (l == 3 ? 2 : 3) : !method_plcg ? 6 : l == 1 ? 4 : 3)
          : !method_plcg ? (d3 ? 6 : 10)
          : l == 1     ? (d3 ? 5 : 6)
          : l == 2     ? (d3 ? 4 : 5)

@@ -263,6 +263,61 @@ void x_updates() {
   }
 }
 
+// The solves that the tests of team launches compare with the oracle and the streaming kernels
+// do run in them, and the next ones that should not do not.
+void which_team() {
+  struct Case {
+    int nx, ny, nz, method, l;
+    bool var, team;
+  };
+  std::vector<Case> cases;
+  const int dims[][3] = {{63, 61, 0}, {64, 75, 0}, {64, 76, 0}, {65, 45, 0},  {65, 61, 0},
+                         {129, 91, 0}, {127, 46, 0}, {40, 300, 0}, {700, 20, 0}, {33, 17, 9},
+                         {64, 16, 31}, {65, 9, 14}, {20, 64, 5}, {130, 7, 13}};
+  for (const auto &d : dims)
+    for (int l = 0; l <= 4; ++l)
+      for (bool var : {false, true}) {
+        const int n = d[0] * d[1] * (d[2] ? d[2] : 1);
+        const int m = l == 0 ? PLCG_METHOD_CG : PLCG_METHOD_PLCG;
+        // CG of a system that the resident kernels take too: only in one workgroup
+        const bool one = l == 0 && !var && n <= PLCG_RESIDENT_MAX && d[0] > 64;
+        cases.push_back({d[0], d[1], d[2], m, l ? l : 1, var, l < 4 && !one});
+      }
+  cases.push_back({20, 20, 0, PLCG_METHOD_PLCG, 2, false, false});       // resident
+  cases.push_back({1, 4000, 0, PLCG_METHOD_PLCG, 2, false, false});
+  cases.push_back({1, 5000, 0, PLCG_METHOD_PLCG, 2, false, true});
+  cases.push_back({2048, 2048, 0, PLCG_METHOD_PLCG, 1, false, false});   // too large
+  std::vector<double> edges((size_t)1 << 17, 1.0);
+  for (const Case &c : cases) {
+    fake::reset();
+    fake::converge_t = 100;
+    plcg_operator_desc op{};
+    op.kind = c.nz ? PLCG_OP_STENCIL3D7 : PLCG_OP_STENCIL2D5;
+    op.nx = c.nx;
+    op.ny = c.ny;
+    op.nz = c.nz ? c.nz : 1;
+    if (c.var) op.cx = op.cy = op.cz = edges.data();
+    if (c.var && !c.nz) op.cz = nullptr;
+    op.jacobi = c.var;
+    plcg_config cfg{};
+    cfg.method = c.method;
+    cfg.l = c.l;
+    cfg.lambda_max = 12.0;
+    cfg.max_restarts = -1;
+    plcg_handle *h = nullptr;
+    EXPECT(plcg_create(&op, &cfg, &h) == PLCG_OK, "%s", plcg_last_error());
+    const size_t n = (size_t)c.nx * c.ny * op.nz;
+    double *b = vec(n), *x = vec(n);
+    plcg_result r{};
+    EXPECT(plcg_solve(h, b, x, 1e-8, 1000, nullptr, &r) == PLCG_OK, "%s", plcg_last_error());
+    EXPECT((fake::count("team") > 0) == c.team, "%d x %d x %d method %d l %d var %d", c.nx, c.ny,
+           c.nz, c.method, c.l, c.var);
+    plcg_destroy(h);
+    free(b);
+    free(x);
+  }
+}
+
 // The five-point matrix of a side x side grid, its rows shuffled within blocks of `block`
 // (1: not): whether a solve runs in a team launch.
 bool rows_team(int side, int block, int l) {
@@ -421,6 +476,7 @@ int main(int argc, char **argv) {
   else if (name == "capture") capture();
   else if (name == "no_mail") no_mail();
   else if (name == "rows_order") rows_order();
+  else if (name == "which_team") which_team();
   else if (name == "x_updates") x_updates();
   else if (name == "single_ticks") single_ticks();
   else if (name == "autotune") autotune();
