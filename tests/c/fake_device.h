@@ -366,7 +366,11 @@ hipError_t launch_plcg_resident(const ResArgs &a, int, int, hipStream_t s) {
 hipError_t launch_cg_resident(const ResArgs &a, int, hipStream_t s) {
   return launch_plcg_resident(a, 0, 0, s);
 }
-hipError_t launch_plcg_team(const TeamArgs &a, int, bool, hipStream_t s) {
+// (method, l, d3: what the launchers have a kernel for)
+static hipError_t fake_team(const TeamArgs &a, bool built, hipStream_t s) {
+  if (!built || a.g.wy * a.g.wz > kTeamWaves || team_tiles(a.g) > kTeamTiles ||
+      team_mail_bytes(a.g) > kTeamMailMax)
+    return hipErrorInvalidValue;
   fake::note("team");
   const bool lose = fake::lose_team;
   const int status = fake::lost_status;
@@ -381,11 +385,20 @@ hipError_t launch_plcg_team(const TeamArgs &a, int, bool, hipStream_t s) {
   });
   return hipSuccess;
 }
-hipError_t launch_cg_team(const TeamArgs &a, bool, hipStream_t s) {
-  return launch_plcg_team(a, 0, false, s);
+static bool fake_width(int method_plcg, int l, bool d3, const TeamArgs &a) {
+  const int v = a.g.v;
+  return v >= 2 && (v <= (method_plcg ? 6 : 8) || (!method_plcg && v == 10)) &&
+         v <= team_vmax(method_plcg, l, d3, a.od.sx != nullptr);
 }
-hipError_t launch_plcg_team_csr(const TeamArgs &a, int, hipStream_t s) {
-  return launch_plcg_team(a, 0, false, s);
+hipError_t launch_plcg_team(const TeamArgs &a, int l, bool d3, hipStream_t s) {
+  return fake_team(a, l >= 1 && l <= 3 && fake_width(1, l, d3, a), s);
+}
+hipError_t launch_cg_team(const TeamArgs &a, bool d3, hipStream_t s) {
+  return fake_team(a, fake_width(0, 1, d3, a), s);
+}
+hipError_t launch_plcg_team_csr(const TeamArgs &a, int l, hipStream_t s) {
+  return fake_team(a, l >= 1 && l <= 3 && ((a.g.v == 2 && a.od.ell_k <= kRowsShort) ||
+                                           (a.g.v == 1 && a.od.ell_k <= kRowsLong)), s);
 }
 
 // ---- batches -------------------------------------------------------------------

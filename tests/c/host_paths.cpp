@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <string>
 #include <thread>
@@ -263,6 +264,37 @@ void x_updates() {
   }
 }
 
+// A solve of a stencil; nz 0: 2D; var: variable coefficients, Jacobi-scaled.
+void solve_stencil(int nx, int ny, int nz, int method, int l, bool var) {
+  static std::vector<double> edges((size_t)3 << 20, 1.0);
+  fake::converge_t = 100;
+  plcg_operator_desc op{};
+  op.kind = nz ? PLCG_OP_STENCIL3D7 : PLCG_OP_STENCIL2D5;
+  op.nx = nx;
+  op.ny = ny;
+  op.nz = nz ? nz : 1;
+  if (var) op.cx = op.cy = edges.data();
+  if (var && nz) op.cz = edges.data();
+  op.jacobi = var;
+  plcg_config cfg{};
+  cfg.method = method;
+  cfg.l = l;
+  cfg.lambda_max = 12.0;
+  cfg.max_restarts = -1;
+  plcg_handle *h = nullptr;
+  plcg_status e = plcg_create(&op, &cfg, &h);
+  EXPECT(e == PLCG_OK, "%d x %d x %d: %s", nx, ny, nz, plcg_last_error());
+  const size_t n = (size_t)nx * ny * op.nz;
+  double *b = vec(n), *x = vec(n);
+  plcg_result r{};
+  e = plcg_solve(h, b, x, 1e-8, 1000, nullptr, &r);
+  EXPECT(e == PLCG_OK, "%d x %d x %d method %d l %d var %d: %s", nx, ny, nz, method, l, var,
+         plcg_last_error());
+  plcg_destroy(h);
+  free(b);
+  free(x);
+}
+
 // The solves that the tests of team launches compare with the oracle and the streaming kernels
 // do run in them, and the next ones that should not do not.
 void which_team() {
@@ -287,35 +319,29 @@ void which_team() {
   cases.push_back({1, 4000, 0, PLCG_METHOD_PLCG, 2, false, false});
   cases.push_back({1, 5000, 0, PLCG_METHOD_PLCG, 2, false, true});
   cases.push_back({2048, 2048, 0, PLCG_METHOD_PLCG, 1, false, false});   // too large
-  std::vector<double> edges((size_t)1 << 17, 1.0);
   for (const Case &c : cases) {
     fake::reset();
-    fake::converge_t = 100;
-    plcg_operator_desc op{};
-    op.kind = c.nz ? PLCG_OP_STENCIL3D7 : PLCG_OP_STENCIL2D5;
-    op.nx = c.nx;
-    op.ny = c.ny;
-    op.nz = c.nz ? c.nz : 1;
-    if (c.var) op.cx = op.cy = op.cz = edges.data();
-    if (c.var && !c.nz) op.cz = nullptr;
-    op.jacobi = c.var;
-    plcg_config cfg{};
-    cfg.method = c.method;
-    cfg.l = c.l;
-    cfg.lambda_max = 12.0;
-    cfg.max_restarts = -1;
-    plcg_handle *h = nullptr;
-    EXPECT(plcg_create(&op, &cfg, &h) == PLCG_OK, "%s", plcg_last_error());
-    const size_t n = (size_t)c.nx * c.ny * op.nz;
-    double *b = vec(n), *x = vec(n);
-    plcg_result r{};
-    EXPECT(plcg_solve(h, b, x, 1e-8, 1000, nullptr, &r) == PLCG_OK, "%s", plcg_last_error());
+    solve_stencil(c.nx, c.ny, c.nz, c.method, c.l, c.var);
     EXPECT((fake::count("team") > 0) == c.team, "%d x %d x %d method %d l %d var %d", c.nx, c.ny,
            c.nz, c.method, c.l, c.var);
-    plcg_destroy(h);
-    free(b);
-    free(x);
   }
+}
+
+// Stencils of any size, method and pipeline length: none is given to a launcher that has no
+// kernel for it.
+void any_stencil() {
+  srand(11);
+  int team = 0;
+  for (int k = 0; k < 1500; ++k) {
+    fake::reset();
+    const bool d3 = rand() % 2;
+    auto side = [&](int hi) { return (int)exp(log((double)hi) * (rand() % 1000) / 999.0); };
+    const int nx = side(d3 ? 130 : 1500), ny = side(d3 ? 130 : 1500), nz = d3 ? side(130) : 0;
+    const int l = rand() % 9;
+    solve_stencil(nx, ny, nz, l ? PLCG_METHOD_PLCG : PLCG_METHOD_CG, l ? l : 1, rand() % 2);
+    team += fake::count("team") > 0;
+  }
+  EXPECT(team > 200, "%d of 1500 in team launches", team);
 }
 
 // The five-point matrix of a side x side grid, its rows shuffled within blocks of `block`
@@ -477,6 +503,7 @@ int main(int argc, char **argv) {
   else if (name == "no_mail") no_mail();
   else if (name == "rows_order") rows_order();
   else if (name == "which_team") which_team();
+  else if (name == "any_stencil") any_stencil();
   else if (name == "x_updates") x_updates();
   else if (name == "single_ticks") single_ticks();
   else if (name == "autotune") autotune();
