@@ -299,7 +299,8 @@ int32_t plcg_version(void);
  * solve of plcg_create + plcg_solve + plcg_destroy in one call, with every
  * workspace buffer (work vectors, partial sums, scalar state, progress record)
  * taken from a static device array of PLCG_NOALLOC_BYTES that each GPU holds
- * from the library's first use of it until the process ends.  It calls no
+ * from the library's first use of it until the process ends (and 32.5 MiB beside
+ * it for what the workgroups of launches that run many iterations exchange).  It calls no
  * hipMalloc, hipFree or other allocating routine.
  *  - op: PLCG_OP_STENCIL2D5 or PLCG_OP_STENCIL3D7 with constant coefficients
  *    only (cx, cy, cz NULL, jacobi 0: the other operators need library copies

@@ -394,7 +394,7 @@ __device__ inline bool halo_y(rsrc_t mail, const Place<V, D3> &pl, int copy, uns
   bool ok = true;
   if constexpr (D3) {
     if (pl.ymail()) {
-      constexpr int C = V < 2 ? 1 : 2;
+      constexpr int C = 2;
 #pragma unroll
       for (int v0 = 0; v0 < V; v0 += C) {
         word4 w[C];
@@ -419,7 +419,7 @@ __device__ inline bool halo_y(rsrc_t mail, const Place<V, D3> &pl, int copy, uns
 // Rows a wave shares with the workgroup's other waves: all of them in 3D (the y
 // neighbours read each), the first and the last in 2D.
 template <int V, bool D3>
-constexpr int shared_rows() { return D3 ? V : V == 1 ? 1 : 2; }
+constexpr int shared_rows() { return D3 ? V : 2; }
 
 template <int V, bool D3, int SR>
 __device__ inline void rows_put(double (*rows)[SR][64], const Place<V, D3> &pl,
@@ -429,7 +429,7 @@ __device__ inline void rows_put(double (*rows)[SR][64], const Place<V, D3> &pl,
     for (int v = 0; v < V; ++v) rows[pl.sw][v][pl.lane] = u[v];
   } else {
     rows[pl.sw][0][pl.lane] = u[0];
-    if (V > 1) rows[pl.sw][SR - 1][pl.lane] = u[V - 1];
+    rows[pl.sw][SR - 1][pl.lane] = u[V - 1];
   }
 }
 
