@@ -423,11 +423,12 @@ plcg_status plcg_batch_get_schedule(const plcg_batch *b, int32_t *cpb);
  * on, e.g. one plcg_batch_autotune chose on an earlier batch of similar systems. */
 plcg_status plcg_batch_set_schedule(plcg_batch *b, const int32_t *cpb);
 
-/* Autotuner of the block-to-system schedule: times `ticks` launches of the
- * systems currently admitted (the launches advance the solves) for each
+/* Autotuner of the block-to-system schedule: times `ticks` ticks of the
+ * systems currently admitted (which advance the solves) for each
  * candidate (1, 2, 4, 8, 16 chunks per workgroup), first one size for every
  * size class, then each class in turn from the largest, and keeps the fastest
- * per active unknown.  Applies to systems admitted later too.  Blocks the host. */
+ * per active unknown.  Applies to systems admitted later too.  Blocks the host.
+ * With no system admitted whose iterations run in ticks it keeps the schedule. */
 plcg_status plcg_batch_autotune(plcg_batch *b, int32_t ticks, void *stream);
 
 plcg_status plcg_batch_destroy(plcg_batch *b);

@@ -935,6 +935,19 @@ plcg_status plcg_batch_autotune(plcg_batch *b, int32_t ticks, void *stream) {
     int32_t e = flush_admissions(b, st);
     if (e != PLCG_OK) return e;
   }
+  // Systems whose sweeps the ticks run; without any the choice stays as it is.
+  auto swept = [&]() {
+    int64_t n = 0;
+    for (size_t s = 0; s < b->slots.size(); ++s)
+      if (b->in_use[s] && b->reports[s].phase != kDone &&
+          (b->slots[s].team == 0 || b->rounds.empty() || b->reports[s].solo != 0))
+        n += b->slots[s].n;
+    return n;
+  };
+  {
+    const int32_t e = run_ticks(b, 2, st);
+    if (e != PLCG_OK || swept() == 0) return e;
+  }
   hipEvent_t e0, e1;
   BHIP(hipEventCreate(&e0));
   BHIP(hipEventCreate(&e1));
@@ -956,11 +969,7 @@ plcg_status plcg_batch_autotune(plcg_batch *b, int32_t ticks, void *stream) {
     int32_t e = apply();
     if (e == PLCG_OK) e = run_ticks(b, 2, st);   // settle: the new partial count reaches the owners
     if (e != PLCG_OK) return e;
-    int64_t active = 0;
-    for (size_t s = 0; s < b->slots.size(); ++s)
-      if (b->in_use[s] && b->reports[s].phase != kDone &&
-          (b->slots[s].team == 0 || b->rounds.empty() || b->reports[s].solo != 0))
-        active += b->slots[s].n;
+    const int64_t active = swept();
     const bool team = !b->rounds.empty();
     if (team && (e = launch_rounds(b, ticks, st)) != PLCG_OK) return e;
     BHIP(hipEventRecord(e0, st));

@@ -469,6 +469,15 @@ void autotune() {
     EXPECT(fake::steps[k] >= trials * 10, "system %d made %d steps in %d trials of 8 + 2", k,
            fake::steps[k], trials);
   plcg_batch_destroy(b);
+  // with nothing that ticks sweep there is nothing to choose
+  fake::reset();
+  b = make_batch(2, 2, 0);
+  add(b, 100, 80, v, 100000);
+  EXPECT(plcg_batch_autotune(b, 8, nullptr) == PLCG_OK, "%s", plcg_last_error());
+  int32_t cpb[3] = {0, 0, 0};
+  plcg_batch_get_schedule(b, cpb);
+  EXPECT(cpb[0] == 4 && cpb[1] == 4 && cpb[2] == 4, "%d %d %d", cpb[0], cpb[1], cpb[2]);
+  plcg_batch_destroy(b);
 }
 
 // On a device with no room for the mail of team launches, a solver is made, and streams (or runs
