@@ -879,7 +879,7 @@ plcg_status solve_cg(plcg_handle *h, const double *b, double *x, double tol, int
   size_t first_launch = tl.launches();
   bool whole = h->res_kind >= 0 && maxit <= kResIterCap;   // all iterations in one launch
   bool team_ran = false;                                   // of a team, already waited for
-  if (h->team && maxit <= kTeamIterCap) {
+  if (h->team && maxit >= 1 && maxit <= kTeamIterCap) {
     if ((e = run_team(h, h->cg_r, x, h->cg_q, maxit, 2 * maxit + 4, s, tl, &whole)) != PLCG_OK)
       return e;
     if (!whole) first_launch = tl.launches();

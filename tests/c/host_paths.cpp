@@ -344,6 +344,18 @@ void any_stencil() {
   EXPECT(team > 200, "%d of 1500 in team launches", team);
 }
 
+// CG without an iteration to make starts no team launch, which would cost it its set-up.
+void no_iterations() {
+  fake::reset();
+  plcg_handle *h = solver(200, 150, PLCG_METHOD_CG, 1);
+  double *b = vec(30000), *x = vec(30000);
+  plcg_result r{};
+  EXPECT(plcg_solve(h, b, x, 1e-8, 0, nullptr, &r) == PLCG_OK, "%s", plcg_last_error());
+  EXPECT(r.iters == 0 && r.reason == PLCG_REASON_MAXIT, "%d %d", r.iters, r.reason);
+  EXPECT(fake::count("team") == 0, "%d", fake::count("team"));
+  plcg_destroy(h);
+}
+
 // The five-point matrix of a side x side grid, its rows shuffled within blocks of `block`
 // (1: not): whether a solve runs in a team launch.
 bool rows_team(int side, int block, int l) {
@@ -511,6 +523,7 @@ int main(int argc, char **argv) {
   else if (name == "capture") capture();
   else if (name == "no_mail") no_mail();
   else if (name == "rows_order") rows_order();
+  else if (name == "no_iterations") no_iterations();
   else if (name == "which_team") which_team();
   else if (name == "any_stencil") any_stencil();
   else if (name == "x_updates") x_updates();
