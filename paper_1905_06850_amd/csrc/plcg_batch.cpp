@@ -535,9 +535,10 @@ int32_t run_plain(plcg_batch *b, int ticks, hipStream_t st, bool team) {
 // move every system as far as a tick for each of the t asked for did, but for one that breaks
 // down on the way: its new start takes three ticks, and the sweeps that it has then left of
 // its t are made in the next step.  A caller of a few ticks wants to
-// look again soon and gets a sweep for each (two for a single one, as the launch and the tick
-// beside it take longer than two ticks did: the burst below served a tick at a time 31.7 ms
-// by ticks alone, 40.0 with one sweep per tick, 22.4 with two); a whole group is worth kTeamSweeps for
+// look again soon and gets a sweep for each, two for up to four, where the launch and the
+// ticks beside it take longer than those that swept did (the burst below served a tick at a
+// time 31.7 ms by ticks alone, 40.0 with one sweep per tick, 22.4 with two; one system of
+// 6 x 11 four at a time 435, 478, 317 us); a whole group is worth kTeamSweeps for
 // each, as loading and storing the vectors, the ticks and the wait (40 us together) would
 // else take as long as the sweeps.  A burst of 24 systems of 32^2 .. 256^2 unknowns, p(2),
 // served 16 ticks at a time: 22.9 ms by ticks alone, 5.9, 4.3, 3.5, 3.1 ms with 1, 2, 4, 8
@@ -576,7 +577,8 @@ int32_t run_ticks(plcg_batch *b, int ticks, hipStream_t st) {
     int32_t e = run_plain(b, lead, st, true);
     while (e == PLCG_OK && ticks > 0) {
       const int t = std::min(ticks, kTeamTicks), report = std::min(t, kTeamSetup);
-      e = launch_rounds(b, t == 1 ? 2 : t < kTeamTicks ? t : kTeamSweeps * t, st);
+      const int sweeps = t < kTeamTicks ? std::max(t, std::min(2 * t, 8)) : kTeamSweeps * t;
+      e = launch_rounds(b, sweeps, st);
       const int after = lean ? report : std::max(t - lead, report);
       if (e == PLCG_OK) e = run_plain(b, after, st, true);
       b->setup_left = std::max(b->setup_left - lead - after, 0);

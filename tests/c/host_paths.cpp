@@ -230,21 +230,22 @@ void turns() {
   }
 }
 
-// A step of one tick costs a team launch beside its tick: it makes two sweeps for them.
-void single_ticks() {
-  fake::reset();
-  double *v = vec(10000);
-  plcg_batch *b = make_batch(2, 1, 0);
-  add(b, 100, 80, v, 1000);
-  plcg_batch_step(b, 4, nullptr);
-  (void)hipStreamSynchronize(nullptr);
-  fake::log.clear();
-  memset(fake::steps, 0, sizeof(fake::steps));
-  for (int k = 0; k < 10; ++k) plcg_batch_step(b, 1, nullptr);
-  (void)hipStreamSynchronize(nullptr);
-  const int launches = fake::count("slots") + fake::count("tick");
-  EXPECT(fake::steps[0] >= launches, "%d sweeps in %d launches", fake::steps[0], launches);
-  plcg_batch_destroy(b);
+// A step of a few ticks costs a team launch beside its ticks: it makes more sweeps for them.
+void few_ticks() {
+  for (int ticks = 1; ticks <= 4; ++ticks) {
+    fake::reset();
+    double *v = vec(10000);
+    plcg_batch *b = make_batch(2, 1, 0);
+    add(b, 100, 80, v, 1000);
+    plcg_batch_step(b, 4, nullptr);
+    (void)hipStreamSynchronize(nullptr);
+    fake::log.clear();
+    memset(fake::steps, 0, sizeof(fake::steps));
+    for (int k = 0; k < 10; ++k) plcg_batch_step(b, ticks, nullptr);
+    (void)hipStreamSynchronize(nullptr);
+    EXPECT(fake::steps[0] >= 20 * ticks, "%d sweeps in steps of %d ticks", fake::steps[0], ticks);
+    plcg_batch_destroy(b);
+  }
 }
 
 // How x was updated, as it is reported: on every iteration by a team launch, on every second
@@ -527,7 +528,7 @@ int main(int argc, char **argv) {
   else if (name == "which_team") which_team();
   else if (name == "any_stencil") any_stencil();
   else if (name == "x_updates") x_updates();
-  else if (name == "single_ticks") single_ticks();
+  else if (name == "few_ticks") few_ticks();
   else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
   else {

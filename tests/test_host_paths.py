@@ -31,7 +31,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["lost_record", "step_counts", "step_counts_lost", "turns", "capture", "autotune",
-                                      "no_mail", "single_ticks", "rows_order", "x_updates", "which_team",
+                                      "no_mail", "few_ticks", "rows_order", "x_updates", "which_team",
                                       "any_stencil", "no_iterations"])
 def test_host_path(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
