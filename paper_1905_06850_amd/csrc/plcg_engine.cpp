@@ -1379,7 +1379,11 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
   // p(2) 2.64 / 1.90, CG 2.78 / 2.28; 70 x 68 p(2) 2.86 / 2.15; 37 x 53 p(1) 2.36 / 2.05,
   // CG 2.37 / 2.23; 16^3 p(2) 3.72 / 3.24; but 20^2 p(2) 2.06 / 2.21, 20 x 90
   // p(2) 2.06 / 2.40 (20 lanes of 64), 12 x 10 x 8 p(2) 2.70 / 3.38, 1 x 4000 p(2) 6.6 / 7.5, and CG over more than one workgroup 2.67 / 3.41
-  // at 100 x 37: its two sums wait for other workgroups.
+  // at 100 x 37: its two sums wait for other workgroups.  CG in 3D stays resident at every
+  // size: in 739 grids of 1536 unknowns and more that one workgroup takes, a team took 0.97 to
+  // 1.51 times as long, 1.17 in the middle (33 x 7 x 7 2.69 / 3.97, 56 x 14 x 2 2.66 / 4.00).
+  // p(2) in 3D goes to a team from 2048 unknowns, 3000 in one or two planes: 29 x 7 x 8 2.37 /
+  // 2.64, 18 x 43 x 2 2.34 / 2.70, 45 x 48 x 1 3.31 / 3.50, but 20 x 39 x 4 2.97 / 2.69.
   const bool stencil = op->kind == PLCG_OP_STENCIL2D5 || op->kind == PLCG_OP_STENCIL3D7;
   const bool rows = op->kind == PLCG_OP_CSR && pl && h->l <= kTeamLMax && h->od.ell_k > 0 &&
                     h->res_kind < 0 && team_rows_pays((int)n, h->l, h->rows_lines);
@@ -1392,8 +1396,9 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
               team_plan(pl ? 1 : 0, h->l, h->d3, h->var, h->op.nx, h->op.ny, h->op.nz, cus,
                         &h->team_geom) &&
               (h->res_kind < 0 ||
-               (n >= kTeamMinUnknowns && h->op.nx >= (pl && h->d3 ? 16 : 32) && n / h->op.nx >= 16 &&
-                (pl || team_tiles(h->team_geom) == 1)));
+               (n >= (pl && h->l == 2 && h->d3 ? (h->op.nz <= 2 ? 3000 : 2048) : kTeamMinUnknowns) &&
+                h->op.nx >= (pl && h->d3 ? 16 : 32) && n / h->op.nx >= 16 &&
+                (pl || (!h->d3 && team_tiles(h->team_geom) == 1))));
   return PLCG_OK;
 }
 

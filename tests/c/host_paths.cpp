@@ -328,6 +328,24 @@ void which_team() {
   }
 }
 
+// Systems in 3D that one workgroup of the resident kernels solves sooner than a team stay there.
+void resident_3d() {
+  const struct {
+    int nx, ny, nz, l;                // l = 0: CG
+    bool team;
+  } cases[] = {{33, 7, 7, 0, false},  {56, 14, 2, 0, false}, {64, 8, 8, 0, false},
+               {16, 17, 17, 0, false}, {65, 9, 9, 0, true},  {16, 16, 16, 1, true},
+               {16, 12, 8, 1, true},  {29, 7, 8, 2, false},  {18, 43, 2, 2, false},
+               {16, 16, 8, 2, true},  {16, 127, 1, 2, false}, {89, 23, 1, 2, false},
+               {45, 48, 1, 2, false}, {50, 60, 1, 2, true},  {20, 39, 4, 2, true},
+               {16, 16, 16, 2, true}, {29, 7, 8, 3, true},   {18, 43, 2, 3, true}};
+  for (const auto &c : cases) {
+    fake::reset();
+    solve_stencil(c.nx, c.ny, c.nz, c.l ? PLCG_METHOD_PLCG : PLCG_METHOD_CG, c.l ? c.l : 1, false);
+    EXPECT((fake::count("team") > 0) == c.team, "%d x %d x %d l %d", c.nx, c.ny, c.nz, c.l);
+  }
+}
+
 // Stencils of any size, method and pipeline length: none is given to a launcher that has no
 // kernel for it.
 void any_stencil() {
@@ -526,6 +544,7 @@ int main(int argc, char **argv) {
   else if (name == "rows_order") rows_order();
   else if (name == "no_iterations") no_iterations();
   else if (name == "which_team") which_team();
+  else if (name == "resident_3d") resident_3d();
   else if (name == "any_stencil") any_stencil();
   else if (name == "x_updates") x_updates();
   else if (name == "few_ticks") few_ticks();
