@@ -1395,7 +1395,7 @@ plcg_status finish_setup(plcg_handle *h, const plcg_operator_desc *op, const plc
     h->team = rows ? team_rows_plan((int)n, h->od.ell_k, cus, &h->team_geom) :
               team_plan(pl ? 1 : 0, h->l, h->d3, h->var, h->op.nx, h->op.ny, h->op.nz, cus,
                         &h->team_geom) &&
-              (h->res_kind < 0 ||
+              (h->res_kind < 0 ? team_grid_pays(pl ? 1 : 0, h->l, h->d3, h->team_geom) :
                (n >= (pl && h->l == 2 && h->d3 ? (h->op.nz <= 2 ? 3000 : 2048) : kTeamMinUnknowns) &&
                 h->op.nx >= (pl && h->d3 ? 16 : 32) && n / h->op.nx >= 16 &&
                 (pl || (!h->d3 && team_tiles(h->team_geom) == 1))));

@@ -237,6 +237,23 @@ inline bool team_plan(int method_plcg, int l, bool d3, bool var, int nx, int ny,
   return false;
 }
 
+// Whether a grid in 3D that the resident kernels do not take is faster in team launches than
+// streaming.  A wave posts 64 lanes of a face however few of them are unknowns, so grids thin
+// along x send mostly empty mail.  us per iteration of CG, team / streaming, by the words that
+// the mail of a sweep has (k = 1024):
+//   nx = 4   250 k 6.49 / 8.93, 394 k 8.23 / 9.31, 441 k 9.11 / 8.92, 494 k 9.27 / 9.16, 510 k
+//            (v = 5) 10.67 / 8.92, 569 k 10.33 / 9.06, 656 k (v = 6) 12.22 / 9.17
+//   nx = 8   441 k 9.15 / 9.26, 478 k 9.71 / 9.19, 510 k (v = 5) 10.62 / 9.17, 656 k 12.20 / 9.96
+//   nx = 16  494 k 9.30 / 9.37, 510 k (v = 5) 10.65 / 9.83, 527 k (v = 4) 9.08 / 9.96, 656 k
+//            12.19 / 11.12;   nx = 24  510 k 10.66 / 11.39, 656 k 12.21 / 13.46
+// p(1) and p(2), with one exchange fewer, only at nx <= 4: p(1) 441 k 6.26 / 6.38, 478 k 6.59 /
+// 6.42, 510 k 6.59 / 6.30, 527 k 6.01 / 6.39, p(2) 459 k 5.56 / 5.69, 478 k 6.12 / 5.71, 525 k
+// 6.35 / 5.55, 527 k 5.67 / 5.74; p(3) never: 527 k 4.85 / 6.42.
+inline bool team_grid_pays(int method_plcg, int l, bool d3, const TeamGeom &g) {
+  if (!d3 || (long long)team_tiles(g) * g.words <= 470 * 1024) return true;
+  return method_plcg ? l >= 3 || g.nx > 4 : g.nx > (g.v >= 5 ? 16 : 8);
+}
+
 // Assembled matrices (their ELL copy of k entries per row): entries per row that the
 // kernels of two widths take, with as many rows per thread as their registers allow.
 constexpr int kRowsShort = 5, kRowsLong = 9;

@@ -346,6 +346,26 @@ void resident_3d() {
   }
 }
 
+// Solves of grids in 3D that are thin along x and would send mostly empty mail stream.
+void thin_3d() {
+  const struct {
+    int nx, ny, nz, l;                // l = 0: CG
+    bool team;
+  } cases[] = {{4, 60, 60, 0, true},    {4, 114, 114, 0, false}, {8, 126, 126, 0, false},
+               {10, 143, 146, 0, false}, {16, 143, 146, 0, false}, {16, 114, 114, 0, true},
+               {24, 143, 146, 0, true}, {146, 143, 10, 0, true}, {4, 114, 114, 1, false},
+               {4, 95, 147, 2, false},  {8, 95, 147, 2, true},   {4, 100, 100, 2, true},
+               {4, 114, 114, 3, true}};
+  for (bool var : {false, true})
+    for (const auto &c : cases) {
+      if (var && c.ny * c.nz > 11000) continue;       // no team plan
+      fake::reset();
+      solve_stencil(c.nx, c.ny, c.nz, c.l ? PLCG_METHOD_PLCG : PLCG_METHOD_CG, c.l ? c.l : 1, var);
+      EXPECT((fake::count("team") > 0) == c.team, "%d x %d x %d l %d var %d", c.nx, c.ny, c.nz,
+             c.l, var);
+    }
+}
+
 // Stencils of any size, method and pipeline length: none is given to a launcher that has no
 // kernel for it.
 void any_stencil() {
@@ -545,6 +565,7 @@ int main(int argc, char **argv) {
   else if (name == "no_iterations") no_iterations();
   else if (name == "which_team") which_team();
   else if (name == "resident_3d") resident_3d();
+  else if (name == "thin_3d") thin_3d();
   else if (name == "any_stencil") any_stencil();
   else if (name == "x_updates") x_updates();
   else if (name == "few_ticks") few_ticks();

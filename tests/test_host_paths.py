@@ -32,7 +32,8 @@ def exe(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", ["lost_record", "step_counts", "step_counts_lost", "turns", "capture", "autotune",
                                       "no_mail", "few_ticks", "rows_order", "x_updates", "which_team",
-                                      "any_stencil", "no_iterations", "resident_3d"])
+                                      "any_stencil", "no_iterations", "resident_3d",
+                                      "thin_3d"])
 def test_host_path(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
