@@ -334,7 +334,7 @@ plcg_status plcg_solve_noalloc(const plcg_operator_desc *op, const plcg_config *
  * step: setup, one p(l)-CG iteration, or the final residual and report.  The
  * iterations of an FP64 system with l = 2 or 3 whose unknowns fit the chip's registers
  * run in launches of their own instead, many to a launch: at least one per tick asked
- * for (not within a stream capture, where the ticks run them).  A
+ * for, up to 64 ahead of their ticks (not within a stream capture, where the ticks run them).  A
  * system's result does not depend on which other systems share the batch.
  * The operator of a batched system is the variable-coefficient Laplacian
  * (A u)_p = sum_q c_pq (u_p - u_q) over the grid edges incident to p (edges to
@@ -392,9 +392,9 @@ plcg_status plcg_batch_add(plcg_batch *b, const plcg_system_desc *sys, const dou
                            uint64_t *ticket);
 
 /* Enqueue what advances every system by at least `ticks` steps on `stream` (returns
- * without waiting).  A system that breaks down on the way and starts again, or whose launch
- * of many iterations could not run (see PLCG_LAUNCH_AUTO), may be left with some of its steps
- * for the next call. */
+ * without waiting), those included that an earlier call's launch of many iterations made ahead.
+ * A system that breaks down on the way and starts again, or whose launch could not run (see
+ * PLCG_LAUNCH_AUTO), may be left with some of its steps for a later call. */
 plcg_status plcg_batch_step(plcg_batch *b, int32_t ticks, void *stream);
 
 /* PLCG_NOT_READY until the system of `ticket` is done; then PLCG_OK with the

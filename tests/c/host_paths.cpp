@@ -95,7 +95,8 @@ uint64_t add(plcg_batch *b, int nx, int ny, double *v, int maxit, hipStream_t s 
   return t;
 }
 
-// Every step moves every system by as many steps as it is asked for, or to its end: systems
+// Steps move every system by as many steps as they are asked for, or to its end, those that
+// earlier ones made ahead of it included: systems
 // that came with this step or an earlier one, that team launches sweep or ticks (lanes mostly
 // idle: the narrow ones), alone or together.  lose: now and then all launches of a step are
 // lost, and the systems that they were to sweep are swept by ticks from the next step on.
@@ -108,6 +109,7 @@ void step_counts(bool lose) {
     const bool narrow = seed / 4 % 2 != 0;
     uint64_t ticket[8] = {0};          // by slot: a system gets the first free one
     bool open[8] = {false};
+    int asked[8], made[8];             // steps since it came
     int room = 8;
     for (int call = 0; call < 12 && good; ++call) {
       for (int want = rand() % 4; want > 0 && room > 0; --want, --room)
@@ -117,6 +119,7 @@ void step_counts(bool lose) {
           ticket[k] = add(b, thin ? 1 : 20 + rand() % 150, thin ? 3000 : 20 + rand() % 150, v,
                           rand() % 60);
           open[k] = true;
+          asked[k] = made[k] = 0;
           break;
         }
       const int sizes[] = {1, 2, 3, 4, 5, 8, 15, 16, 17, 31, 40};
@@ -129,8 +132,11 @@ void step_counts(bool lose) {
         if (!open[k]) continue;
         plcg_result r{};
         const bool done = plcg_batch_poll(b, ticket[k], &r) == PLCG_OK;
-        EXPECT(done || fake::lose_slots || fake::steps[k] >= ticks, "seed %d call %d: system %d made %d of %d steps",
-               seed, call, k, fake::steps[k], ticks);
+        asked[k] += ticks;
+        made[k] += fake::steps[k];
+        if (fake::lose_slots) asked[k] = std::min(asked[k], made[k]);
+        EXPECT(done || made[k] >= asked[k], "seed %d call %d: system %d made %d of %d steps", seed,
+               call, k, made[k], asked[k]);
         if (done) {
           open[k] = false;
           ++room;
@@ -244,6 +250,32 @@ void few_ticks() {
     for (int k = 0; k < 10; ++k) plcg_batch_step(b, ticks, nullptr);
     (void)hipStreamSynchronize(nullptr);
     EXPECT(fake::steps[0] >= 20 * ticks, "%d sweeps in steps of %d ticks", fake::steps[0], ticks);
+    plcg_batch_destroy(b);
+  }
+}
+
+// In steps of a few ticks of a batch some of whose systems ticks sweep, the team launches of the
+// others come once in sixteen ticks, and new systems are swept as soon as their setup is done.
+void few_ticks_mixed() {
+  for (int ticks : {1, 2, 4, 8}) {
+    fake::reset();
+    double *v = vec(20000);
+    plcg_batch *b = make_batch(2, 3, 0);
+    add(b, 1, 3000, v, 1000000);
+    add(b, 100, 80, v, 1000000);
+    plcg_batch_step(b, 4, nullptr);
+    (void)hipStreamSynchronize(nullptr);
+    fake::log.clear();
+    for (int k = 0; k < 160; k += ticks) plcg_batch_step(b, ticks, nullptr);
+    (void)hipStreamSynchronize(nullptr);
+    const int slots = fake::count("slots");
+    EXPECT(slots >= 9 && slots <= 11, "%d launches in 160 ticks, %d at a time", slots, ticks);
+    EXPECT(fake::steps[1] >= 4 * 140, "%d sweeps", fake::steps[1]);
+    plcg_batch_step(b, 1, nullptr);        // a launch may have been made just now
+    add(b, 90, 70, v, 1000000);
+    for (int k = 0; k < 6; ++k) plcg_batch_step(b, ticks, nullptr);
+    (void)hipStreamSynchronize(nullptr);
+    EXPECT(fake::steps[2] >= 64, "new system: %d steps", fake::steps[2]);
     plcg_batch_destroy(b);
   }
 }
@@ -569,6 +601,7 @@ int main(int argc, char **argv) {
   else if (name == "any_stencil") any_stencil();
   else if (name == "x_updates") x_updates();
   else if (name == "few_ticks") few_ticks();
+  else if (name == "few_ticks_mixed") few_ticks_mixed();
   else if (name == "autotune") autotune();
   else if (name == "step_counts_lost") step_counts(true);
   else {

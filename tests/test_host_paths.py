@@ -31,7 +31,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["lost_record", "step_counts", "step_counts_lost", "turns", "capture", "autotune",
-                                      "no_mail", "few_ticks", "rows_order", "x_updates", "which_team",
+                                      "no_mail", "few_ticks", "few_ticks_mixed", "rows_order", "x_updates", "which_team",
                                       "any_stencil", "no_iterations", "resident_3d",
                                       "thin_3d"])
 def test_host_path(exe, scenario):
