@@ -88,7 +88,9 @@ enum { PLCG_PREC_FP64 = 0, PLCG_PREC_FP32_REFINED = 1 };
  *   plcg_resident_supported).
  * AUTO (default): RESIDENT where it is available, else STREAMING - or, for FP64 solves
  *   of the constant and the Jacobi-scaled variable stencils from 1536 to about a million
- *   unknowns (CG, p(1) .. p(3), x_update AUTO, at most 2^20 iterations) and of CSR matrices
+ *   unknowns (CG, p(1) .. p(3), x_update AUTO, at most 2^20 iterations; not CG in 3D and small
+ *   p(2) in 3D where RESIDENT is available, nor large grids in 3D with few unknowns along x)
+ *   and of CSR matrices
  *   with up to nine entries per row and 490 thousand rows (250 thousand beyond five
  *   entries; p(1) .. p(3); not where the order of 24 to 250 thousand rows scatters their
  *   columns), one launch per run of up to one workgroup per CU, the vectors
